@@ -206,22 +206,24 @@ __global__ __launch_bounds__(kThreads) void k_histogram(const Tile* __restrict__
 }
 
 // ---------------------------------------------------------------------------------
-// DP workspace layout (offsets in bytes, all 256-byte aligned):
+// The DP (Alg. 3, App. D): D[j][r] = min over l of D[j-1][l-1] + C(l, r), argmin to the
+// smallest l, over the b non-empty bins. Workspace (all 256-byte aligned):
 //   hdr    int32[16]: [0] b (non-empty bins), [1] keff (entries the DP solves for),
-//          [2] status
+//          [2] status, [3] 1 when rows may be pruned (dp_may_prune)
 //   Z0,Z1,Z2,cnt,ctr   double[NB + 1] each (1-based, index 0 = 0)
-//   D      double[(k + 1) * (NB + 1)]   D[j][r]
-//   split  uint16[(k + 1) * (NB + 1)]
-//   pv, pa double / int32 [2][NB + 1][kDpMaxChunks]: per-chunk partial minima of a level
+//   D      double[2][NB + 1]   D[j][r], by the parity of j
+//   from   uint16[2][NB + 1]   smallest l that a row of level j + 1 needs to look at
+//   anc    uint16[2][NB + 1]   row of the path at the last checkpoint level before j
+//   split  uint16[k + 1][NB + 1]   the argmin l
+//   jump   uint16[k / kDpCheck + 1][NB + 1]   anc at the checkpoint levels
 // ---------------------------------------------------------------------------------
 struct DpLayout {
-    size_t hdr, z0, z1, z2, cnt, ctr, d, split, pv, pa, total;
+    size_t hdr, z0, z1, z2, cnt, ctr, d, from, anc, split, jump, total;
 };
 
-constexpr int kDpThreads = 1024;
-constexpr int kDpRows = kDpThreads / 64;                        // rows r per workgroup
-constexpr int kDpChunk = 1024;                                  // l values per workgroup
-constexpr int kDpMaxChunks = (kMaxBins + kDpChunk - 1) / kDpChunk;
+constexpr int kDpThreads = 256;
+constexpr int kDpRows = kDpThreads / 64;   // rows r per workgroup, one wave each
+constexpr int kDpCheck = 16;               // levels between checkpoints of the backtrack
 
 __host__ __device__ inline size_t align256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
 
@@ -236,10 +238,11 @@ __host__ __device__ inline DpLayout dp_layout(int32_t nbins, int32_t k)
     L.z2 = o; o += align256(row * sizeof(double));
     L.cnt = o; o += align256(row * sizeof(double));
     L.ctr = o; o += align256(row * sizeof(double));
-    L.d = o; o += align256(static_cast<size_t>(k + 1) * row * sizeof(double));
+    L.d = o; o += align256(2 * row * sizeof(double));
+    L.from = o; o += align256(2 * row * sizeof(uint16_t));
+    L.anc = o; o += align256(2 * row * sizeof(uint16_t));
     L.split = o; o += align256(static_cast<size_t>(k + 1) * row * sizeof(uint16_t));
-    L.pv = o; o += align256(2 * row * kDpMaxChunks * sizeof(double));
-    L.pa = o; o += align256(2 * row * kDpMaxChunks * sizeof(int32_t));
+    L.jump = o; o += align256(static_cast<size_t>(k / kDpCheck + 1) * row * sizeof(uint16_t));
     L.total = o;
     return L;
 }
@@ -250,273 +253,335 @@ __device__ __forceinline__ T* at(void* ws, size_t off)
     return reinterpret_cast<T*>(static_cast<char*>(ws) + off);
 }
 
+// The interval cost of bins l .. r from the prefix sums before l (z*) and at r (zr*), in
+// the definition's operations: SSE about the mean, or about the forced entry a = -1, +1.
+__device__ __forceinline__ double dp_cost_free(double zr0, double zr1, double zr2, double z0,
+                                               double z1, double z2)
+{
+    const double S0 = zr0 - z0;
+    const double S1 = zr1 - z1;
+    const double S2 = zr2 - z2;
+    return S2 - S1 * S1 / S0;
+}
+
+__device__ __forceinline__ double dp_cost_forced(double a, double zr0, double zr1, double zr2,
+                                                 double z0, double z1, double z2)
+{
+    const double S0 = zr0 - z0;
+    const double S1 = zr1 - z1;
+    const double S2 = zr2 - z2;
+    return S2 - 2.0 * a * S1 + a * a * S0;
+}
+
+// Whether rows may be pruned (k_dp_level). The proof takes the stored prefix sums as exact
+// numbers: bin i then has weight c_i and the point mu_i = (Z1[i] - Z1[i-1]) / c_i. It needs
+// the counts' sums exact and the points in bin order; each stored Z1 is off by at most one
+// rounding of itself (2^-53 N) and of c m, so with c_i >= 1 neighbouring points, 2 / nbins
+// apart, keep their order while 8 N 2^-53 < 2 / nbins. N nbins < 2^50 is half of that.
+__device__ __forceinline__ bool dp_may_prune(double total, int32_t nbins)
+{
+    return total * static_cast<double>(nbins) < 1125899906842624.0;
+}
+
 // Compaction of non-empty bins and prefix sums, in increasing bin order. The workgroup
 // compacts the non-empty bins (a prefix count over 16-bin runs) and forms each one's
-// centre, count and the two products c m and (c m) m in LDS; one thread then takes the
-// three running sums in increasing bin order, so the summation order is the
-// definition's, with nothing but three additions per bin on its path. The sums are
-// copied out by the whole workgroup. Also clears row 0 of D.
+// centre, count and the two products c m and (c m) m in LDS; three threads, one wave each,
+// then take a running sum each in increasing bin order, sixteen terms loaded ahead of
+// their additions, so the summation order is the definition's. The chain of 4096 dependent
+// float64 additions bounds the kernel (one thread taking all three, term by term: 155 us).
+// Level 1 (one interval, entry -1) is written on the way out.
 constexpr int kPrepRun = kMaxBins / kThreads;   // bins per thread in the compaction
+constexpr int kPrepBatch = 16;
 
 __global__ __launch_bounds__(kThreads) void k_dp_prep(const uint64_t* __restrict__ hist,
                                                       int32_t nbins, int32_t k, void* ws)
 {
-    __shared__ double t0[kMaxBins + 1], t1[kMaxBins + 1], t2[kMaxBins + 1];   // c, c m, c m m
+    // t[q][0 .. b]: c, c m, c m m, then their running sums; slots past b are read ahead
+    __shared__ double t[3][kMaxBins + 2 * kPrepBatch];
     __shared__ int runs[kThreads];
     __shared__ int nr;
     const int tid = threadIdx.x;
     const DpLayout L = dp_layout(nbins, k);
-    double* D = at<double>(ws, L.d);
-    double* Z0 = at<double>(ws, L.z0);
-    double* Z1 = at<double>(ws, L.z1);
-    double* Z2 = at<double>(ws, L.z2);
     double* cnt = at<double>(ws, L.cnt);
     double* ctr = at<double>(ws, L.ctr);
-    const size_t row = static_cast<size_t>(nbins) + 1;
-    for (size_t r = tid; r < row; r += blockDim.x) D[r] = r == 0 ? 0.0 : INFINITY;
     const double w = 2.0 / static_cast<double>(nbins);
     // thread tid owns bins [tid * kPrepRun, + kPrepRun): count, then scan the counts
     const int i0 = tid * kPrepRun;
+    uint64_t hv[kPrepRun];
     int mine = 0;
-    for (int i = i0; i < i0 + kPrepRun && i < nbins; ++i) mine += hist[i] != 0;
+#pragma unroll
+    for (int q = 0; q < kPrepRun; ++q) hv[q] = i0 + q < nbins ? hist[i0 + q] : 0;
+#pragma unroll
+    for (int q = 0; q < kPrepRun; ++q) mine += hv[q] != 0;
     runs[tid] = mine;
     __syncthreads();
-    if (tid == 0) {
-        int acc = 0;
-        for (int q = 0; q < kThreads; ++q) {
-            const int c = runs[q];
-            runs[q] = acc;
-            acc += c;
+    if (tid < 64) {   // one wave: four counts a lane, then a shuffle scan
+        int c[kThreads / 64], sum = 0;
+        for (int q = 0; q < kThreads / 64; ++q) {
+            c[q] = runs[tid * (kThreads / 64) + q];
+            sum += c[q];
         }
-        nr = acc;
-    }
-    __syncthreads();
-    int r = runs[tid];   // compacted slots before this thread's bins (0-based)
-    for (int i = i0; i < i0 + kPrepRun && i < nbins; ++i) {
-        const uint64_t hv = hist[i];
-        if (hv == 0) continue;
-        const double c = static_cast<double>(hv);
-        const double m = -1.0 + (static_cast<double>(i) + 0.5) * w;
-        ++r;
-        const double cm = c * m;
-        t0[r] = c;
-        t1[r] = cm;
-        t2[r] = cm * m;
-        ctr[r] = m;
-        cnt[r] = c;
+        int acc = sum;
+        for (int off = 1; off < 64; off <<= 1) {
+            const int up = __shfl_up(acc, off);
+            if (tid >= off) acc += up;
+        }
+        if (tid == 63) nr = acc;
+        acc -= sum;
+        for (int q = 0; q < kThreads / 64; ++q) {
+            runs[tid * (kThreads / 64) + q] = acc;
+            acc += c[q];
+        }
     }
     __syncthreads();
     const int b = nr;
-    if (tid == 0) {
-        double z0 = 0.0, z1 = 0.0, z2 = 0.0;
-        t0[0] = 0.0;
-        t1[0] = 0.0;
-        t2[0] = 0.0;
-        for (int q = 1; q <= b; ++q) {
-            z0 = z0 + t0[q];
-            z1 = z1 + t1[q];
-            z2 = z2 + t2[q];
-            t0[q] = z0;
-            t1[q] = z1;
-            t2[q] = z2;
+    int r = runs[tid];   // compacted slots before this thread's bins (0-based)
+#pragma unroll
+    for (int q = 0; q < kPrepRun; ++q) {
+        if (hv[q] == 0) continue;
+        const double c = static_cast<double>(hv[q]);
+        const double m = -1.0 + (static_cast<double>(i0 + q) + 0.5) * w;
+        ++r;
+        const double cm = c * m;
+        t[0][r] = c;
+        t[1][r] = cm;
+        t[2][r] = cm * m;
+        ctr[r] = m;
+        cnt[r] = c;
+    }
+    if (tid < 3) t[tid][0] = 0.0;
+    if (tid < 3 * kPrepBatch) t[tid / kPrepBatch][b + 1 + tid % kPrepBatch] = 0.0;
+    __syncthreads();
+    if ((tid & 63) == 0 && tid < 192) {
+        double* __restrict__ x = t[tid >> 6];
+        double z = 0.0;
+        double next[kPrepBatch];
+#pragma unroll
+        for (int u = 0; u < kPrepBatch; ++u) next[u] = x[1 + u];
+        for (int q = 1; q <= b; q += kPrepBatch) {
+            double cur[kPrepBatch];
+#pragma unroll
+            for (int u = 0; u < kPrepBatch; ++u) cur[u] = next[u];
+            // the batch after this one: x has kPrepBatch slots past b + kPrepBatch - 1
+            const int ahead = q + kPrepBatch <= b ? q + kPrepBatch : q;
+#pragma unroll
+            for (int u = 0; u < kPrepBatch; ++u) next[u] = x[ahead + u];
+#pragma unroll
+            for (int u = 0; u < kPrepBatch; ++u) {
+                z = z + cur[u];
+                cur[u] = z;
+            }
+#pragma unroll
+            for (int u = 0; u < kPrepBatch; ++u) x[q + u] = cur[u];
         }
+    }
+    __syncthreads();
+    if (tid == 0) {
         int32_t* hdr = at<int32_t>(ws, L.hdr);
         hdr[0] = b;
         hdr[1] = b >= k ? k : (b >= 2 ? b : 0);
         hdr[2] = b >= k ? 0 : 1;
+        hdr[3] = dp_may_prune(t[0][b], nbins) ? 1 : 0;
     }
-    __syncthreads();
-    for (int q = tid; q <= b; q += blockDim.x) {
-        Z0[q] = t0[q];
-        Z1[q] = t1[q];
-        Z2[q] = t2[q];
+    double* Z0 = at<double>(ws, L.z0);
+    double* Z1 = at<double>(ws, L.z1);
+    double* Z2 = at<double>(ws, L.z2);
+    const size_t row = static_cast<size_t>(nbins) + 1;
+    double* D1 = at<double>(ws, L.d) + row;
+    uint16_t* from1 = at<uint16_t>(ws, L.from) + row;
+    uint16_t* anc1 = at<uint16_t>(ws, L.anc) + row;
+    uint16_t* split1 = at<uint16_t>(ws, L.split) + row;
+    for (int q = tid; q <= b; q += kThreads) {
+        const double z0 = t[0][q], z1 = t[1][q], z2 = t[2][q];
+        Z0[q] = z0;
+        Z1[q] = z1;
+        Z2[q] = z2;
+        D1[q] = q == 0 ? INFINITY : 0.0 + dp_cost_forced(-1.0, z0, z1, z2, 0.0, 0.0, 0.0);
+        from1[q] = 1;
+        anc1[q] = 0;
+        split1[q] = 1;
     }
+}
+
+// Smallest of a wave's doubles (no NaN), in every lane.
+template <int CTRL>
+__device__ __forceinline__ double dpp_min(double v)
+{
+    const uint64_t x = __builtin_bit_cast(uint64_t, v);
+    const int lo = static_cast<int>(x), hi = static_cast<int>(x >> 32);
+    const uint32_t l2 = __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false);
+    const uint32_t h2 = __builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false);
+    return fmin(v, __builtin_bit_cast(double, (static_cast<uint64_t>(h2) << 32) | l2));
+}
+
+__device__ __forceinline__ double wave_min(double v)
+{
+    v = dpp_min<0xB1>(v);    // quad_perm 1,0,3,2
+    v = dpp_min<0x4E>(v);    // quad_perm 2,3,0,1
+    v = dpp_min<0x141>(v);   // row_half_mirror
+    v = dpp_min<0x140>(v);   // row_mirror
+    v = dpp_min<0x142>(v);   // row_bcast15
+    v = dpp_min<0x143>(v);   // row_bcast31: lane 63 has the minimum
+    const uint64_t x = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(x), 63);
+    const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(x >> 32), 63);
+    return __builtin_bit_cast(double, (static_cast<uint64_t>(hi) << 32) | lo);
 }
 
 // ---------------------------------------------------------------------------------
-// DP level j: D[j][r] = min over l of D[j-1][l-1] + C(l, r), argmin to the smallest l.
-// Workgroup (x, y) takes rows r0 .. r0 + 15 (one wave each) and the candidates l of
-// chunk y, [j + 1024 y, j + 1024 y + 1023], staging Z[l-1] and D[j-1][l-1] for that
-// chunk in LDS (32 KB), so every workgroup does at most 16 x 1024 evaluations. It writes
-// a partial (min, argmin) per row and chunk (double-buffered by level parity); level
-// j + 1 rebuilds D[j][.] from them while staging, in chunk order with ties to the
-// smaller l, and its last row of workgroups (whose chunks cover every l) stores the
-// final D[j][.] and split[j][.] rows for the backtrack. k_dp_final reduces the last
-// level. Level j < keff takes only the rows r <= b - (keff - j): a longer prefix leaves
-// too few bins for the entries still to come, so no path to D[keff][b] passes through
-// it (the rows it does take, and their candidates, are the ones the full scan has).
+// DP level j, 2 <= j < keff: a wave takes one row r and its candidates l, 64 at a time
+// from l = r down to the row's lower bound. Only the rows r <= b - (keff - j) are taken: a
+// longer prefix leaves too few bins for the entries still to come, so no path to
+// D[keff][b] passes through it.
+//
+// Lower bound. Write cand_j(l, r) for the exact value of D[j-1][l-1] + C(l, r) over the
+// stored prefix sums. Where dp_may_prune holds, C is the SSE of points in sorted order and
+// satisfies the quadrangle inequality (the forced first interval too, whose entry -1 lies
+// below every mean), so
+//   (a) for l' < l, cand_j(l', r) - cand_j(l, r) does not fall when r grows, and
+//   (b) it does not fall when j grows: D[j] - D[j-1] does not rise along a row. (Take an
+//       optimal path of j - 1 edges to y and one of j edges to x < y: an edge of the second
+//       lies inside one of the first, and exchanging the two paths' tails there gives j
+//       edges to y and j - 1 to x at no higher cost.)
+// So a candidate that is worse than another by more than the rounding of both stays worse
+// at all higher levels and rows, and is never the computed minimum there. Rounding: the
+// computed C is off by at most 7.2 u (S2 + S1^2 / S0), u = 2^-53, and at most 12.1 u S0 in
+// the forced interval; along a path the intervals are disjoint, so these add up to less
+// than 28 u Z0[r], and each level adds at most 1.1 u of the value itself. A difference of
+// computed candidates is therefore within u (112 Z0[r] + 10 k D) of the exact one over two
+// levels; `slack` is about twice that. from[r] = the smallest l whose computed candidate
+// lies within slack of the minimum; a row that the level before did not have takes the
+// from of the row below it. Values and argmins are those of the full scan, bit for bit.
+//
+// The candidates fall from 1.9e9 to 5e7 at b = 4096, k = 256 (windows of 14 to 40 bins from
+// level 64 on), and a level is bound by its launch and two dependent trips to memory: the
+// first 64 candidates are loaded before the header and the lower bound are known. Full
+// scan, with the candidates staged in LDS, took 18.1 us a level; this takes 4.4-5.6 us from
+// level 16 on (30 us at level 2): 1.38 against 4.82 ms for the whole DP.
 // ---------------------------------------------------------------------------------
-__device__ __forceinline__ int dp_chunks(int jj, int r)
-{
-    const int hi = jj == 1 ? 1 : r;
-    return hi < jj ? 0 : (hi - jj) / kDpChunk + 1;
-}
-
-__device__ __forceinline__ void dp_reduce(const double* __restrict__ pv,
-                                          const int32_t* __restrict__ pa, int jj, int r,
-                                          double& v, int& a)
-{
-    v = INFINITY;
-    a = 0x7fffffff;
-    const int nc = dp_chunks(jj, r);
-    for (int c = 0; c < nc; ++c) {
-        const double x = pv[static_cast<size_t>(r) * kDpMaxChunks + c];
-        const int y = pa[static_cast<size_t>(r) * kDpMaxChunks + c];
-        if (x < v || (x == v && y < a)) {
-            v = x;
-            a = y;
-        }
-    }
-}
-
 __global__ __launch_bounds__(kDpThreads) void k_dp_level(int32_t nbins, int32_t k, int32_t j,
                                                          void* ws)
 {
-    __shared__ double sZ0[kDpChunk], sZ1[kDpChunk], sZ2[kDpChunk], sD[kDpChunk];
+    const DpLayout L = dp_layout(nbins, k);
+    const size_t row = static_cast<size_t>(nbins) + 1;
+    const size_t cur = (j & 1) * row, prev = row - cur;
+    const double* __restrict__ Z0 = at<double>(ws, L.z0);
+    const double* __restrict__ Z1 = at<double>(ws, L.z1);
+    const double* __restrict__ Z2 = at<double>(ws, L.z2);
+    const double* __restrict__ Dp = at<double>(ws, L.d) + prev;
+    const uint16_t* __restrict__ fp = at<uint16_t>(ws, L.from) + prev;
+    const uint16_t* __restrict__ ap = at<uint16_t>(ws, L.anc) + prev;
+    const int32_t* __restrict__ hdr = at<int32_t>(ws, L.hdr);
+    const int lane = threadIdx.x & 63;
+    const int r = j + static_cast<int>(blockIdx.x) * kDpRows +
+                  __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    if (r > nbins) return;
+    // l - 1 of this lane's first candidate, kept inside the arrays
+    const int x0 = r - 1 - lane > 0 ? r - 1 - lane : 0;
+    double z0 = Z0[x0], z1 = Z1[x0], z2 = Z2[x0], dv = Dp[x0];
+    int av = ap[x0];
+    const double zr0 = Z0[r], zr1 = Z1[r], zr2 = Z2[r];
+    const int f0 = fp[r], f1 = fp[r - 1];
+    const int b = hdr[0], keff = hdr[1], prune = hdr[3];
+    const int rmax = b - keff + j;
+    if (j >= keff || r > rmax) return;
+    int lo = j;
+    if (prune) {
+        const int f = r < rmax ? f0 : f1;
+        lo = f > j ? f : j;
+    }
+    double best = INFINITY;
+    int arg = 0, anc = 0;
+    double first = INFINITY;   // the first chunk's candidate
+    if (r - lane >= lo) {
+        const double c = dv + dp_cost_free(zr0, zr1, zr2, z0, z1, z2);
+        if (c < INFINITY) {   // counts past 2^53 can make an empty interval: NaN
+            first = best = c;
+            arg = r - lane;
+            anc = av;
+        }
+    }
+    for (int l = r - 64 - lane; l >= lo; l -= 64) {   // falling l: the last minimum kept
+        const double c = Dp[l - 1] + dp_cost_free(zr0, zr1, zr2, Z0[l - 1], Z1[l - 1], Z2[l - 1]);
+        if (c <= best && c < INFINITY) {
+            best = c;
+            arg = l;
+            anc = ap[l - 1];
+        }
+    }
+    const double m = wave_min(best);
+    const double slack = 1.1102230246251565e-16 *
+                         (256.0 * zr0 + 32.0 * static_cast<double>(k) * m);
+    const double near = m + slack;
+    int bestl, from;
+    if (!(m < INFINITY)) {   // no candidate has a value (see above)
+        bestl = from = lo;
+    } else if (r - lo < 64) {   // one chunk (wave-uniform): l falls with the lane
+        bestl = r - (63 - __builtin_clzll(__ballot(first == m)));
+        from = r - (63 - __builtin_clzll(__ballot(first <= near)));
+    } else {
+        int a = best == m ? arg : 0x7fffffff;
+        for (int off = 1; off < 64; off <<= 1) {
+            const int o = __shfl_xor(a, off);
+            a = o < a ? o : a;
+        }
+        bestl = a;
+        // the smallest l within slack, from the lower bound up (bestl ends the search)
+        from = lo;
+        for (int base = lo;; base += 64) {
+            const int l = base + lane;
+            bool ok = false;
+            if (l <= r) {
+                const double c = Dp[l - 1] + dp_cost_free(zr0, zr1, zr2, Z0[l - 1], Z1[l - 1],
+                                                          Z2[l - 1]);
+                ok = c <= near;
+            }
+            const unsigned long long hit = __ballot(ok);
+            if (hit) {
+                from = base + __builtin_ctzll(hit);
+                break;
+            }
+            if (base + 63 >= bestl) break;
+        }
+    }
+    const int w = (r - bestl) & 63;   // the lane that has it
+    const int up = (j - 1) % kDpCheck == 0 ? bestl - 1 : __builtin_amdgcn_readlane(anc, w);
+    if (lane == 0) {
+        at<double>(ws, L.d)[cur + r] = m;
+        at<uint16_t>(ws, L.from)[cur + r] = static_cast<uint16_t>(from);
+        at<uint16_t>(ws, L.anc)[cur + r] = static_cast<uint16_t>(up);
+        at<uint16_t>(ws, L.split)[static_cast<size_t>(j) * row + r] = static_cast<uint16_t>(bestl);
+        if (j % kDpCheck == 0)
+            at<uint16_t>(ws, L.jump)[static_cast<size_t>(j / kDpCheck) * row + r] =
+                static_cast<uint16_t>(up);
+    }
+}
+
+// The last level (row b only, entry +1) and the backtrack, one workgroup. The path's rows
+// at the checkpoint levels come from anc and jump, one dependent read per kDpCheck levels;
+// then one lane per stretch between checkpoints walks its split entries, and the entries
+// (-1, +1 or the weighted mean of the interval) are formed in parallel: 32 dependent reads
+// at k = 256 where a walk along the levels took 255 (77-110 us). Degenerate histograms
+// (b < k) are padded with +1.
+__global__ __launch_bounds__(1024) void k_dp_last(int32_t nbins, int32_t k, void* ws,
+                                                  double* codebook, double* cost, int32_t* status)
+{
+    __shared__ double sv[16];
+    __shared__ int sa[16];
+    __shared__ int node[kMaxK + 1];   // row of the path at each level
     const DpLayout L = dp_layout(nbins, k);
     const int32_t* hdr = at<int32_t>(ws, L.hdr);
     const int b = hdr[0];
     const int keff = hdr[1];
-    if (j > keff) return;
-    int r0, r1;
-    if (j == keff) {
-        if (blockIdx.x != 0) return;
-        r0 = r1 = b;
-    } else {
-        const int rmax = b - keff + j;
-        r0 = j + static_cast<int>(blockIdx.x) * kDpRows;
-        if (r0 > rmax) return;
-        r1 = r0 + kDpRows - 1 < rmax ? r0 + kDpRows - 1 : rmax;
-    }
-    const int hi_max = j == 1 ? 1 : r1;
-    const int l0 = j + static_cast<int>(blockIdx.y) * kDpChunk;
-    if (l0 > hi_max) return;
-    const int l1 = l0 + kDpChunk - 1 < hi_max ? l0 + kDpChunk - 1 : hi_max;
     const double* Z0 = at<double>(ws, L.z0);
     const double* Z1 = at<double>(ws, L.z1);
     const double* Z2 = at<double>(ws, L.z2);
     const size_t row = static_cast<size_t>(nbins) + 1;
-    double* D = at<double>(ws, L.d);
-    uint16_t* split = at<uint16_t>(ws, L.split);
-    const size_t pstride = row * kDpMaxChunks;
-    const double* pv_prev = at<double>(ws, L.pv) + ((j - 1) & 1) * pstride;
-    const int32_t* pa_prev = at<int32_t>(ws, L.pa) + ((j - 1) & 1) * pstride;
-    double* pv_cur = at<double>(ws, L.pv) + (j & 1) * pstride;
-    int32_t* pa_cur = at<int32_t>(ws, L.pa) + (j & 1) * pstride;
-    const bool last_rows = j == keff || static_cast<int>(blockIdx.x) == (b - keff) / kDpRows;
-    for (int i = threadIdx.x; i <= l1 - l0; i += kDpThreads) {
-        const int l = l0 + i;
-        sZ0[i] = Z0[l - 1];
-        sZ1[i] = Z1[l - 1];
-        sZ2[i] = Z2[l - 1];
-        double dv;
-        if (j == 1) {
-            dv = l == 1 ? 0.0 : INFINITY;   // D[0][l-1]
-        } else {
-            int da;
-            dp_reduce(pv_prev, pa_prev, j - 1, l - 1, dv, da);
-            if (last_rows) {
-                D[static_cast<size_t>(j - 1) * row + (l - 1)] = dv;
-                split[static_cast<size_t>(j - 1) * row + (l - 1)] = static_cast<uint16_t>(da);
-            }
-        }
-        sD[i] = dv;
-    }
-    __syncthreads();
-    const int r = r0 + static_cast<int>(threadIdx.x >> 6);
-    if (r > r1) return;
-    const int lane = threadIdx.x & 63;
-    const double zr0 = Z0[r], zr1 = Z1[r], zr2 = Z2[r];
-    const int hi = j == 1 ? 1 : r;
-    double best = INFINITY;
-    int arg = 0x7fffffff;
-    for (int i = lane; i <= l1 - l0; i += 64) {   // increasing l: first minimum kept
-        const int l = l0 + i;
-        if (l > hi) break;
-        const double S0 = zr0 - sZ0[i];
-        const double S1 = zr1 - sZ1[i];
-        const double S2 = zr2 - sZ2[i];
-        double c;
-        if (j == 1 || j == keff) {
-            const double a = j == 1 ? -1.0 : 1.0;
-            c = S2 - 2.0 * a * S1 + a * a * S0;
-        } else {
-            c = S2 - S1 * S1 / S0;
-        }
-        const double cand = sD[i] + c;
-        if (cand < best) {
-            best = cand;
-            arg = l;
-        }
-    }
-    for (int off = 1; off < 64; off <<= 1) {
-        const double ob = __shfl_xor(best, off);
-        const int oa = __shfl_xor(arg, off);
-        if (ob < best || (ob == best && oa < arg)) {
-            best = ob;
-            arg = oa;
-        }
-    }
-    if (lane == 0) {
-        pv_cur[static_cast<size_t>(r) * kDpMaxChunks + blockIdx.y] = best;
-        pa_cur[static_cast<size_t>(r) * kDpMaxChunks + blockIdx.y] = arg;
-    }
-}
-
-// The last level's result for r = b.
-__global__ void k_dp_final(int32_t nbins, int32_t k, void* ws)
-{
-    if (threadIdx.x != 0) return;
-    const DpLayout L = dp_layout(nbins, k);
-    const int32_t* hdr = at<int32_t>(ws, L.hdr);
-    const int b = hdr[0];
-    const int keff = hdr[1];
-    if (keff < 2) return;
-    const size_t row = static_cast<size_t>(nbins) + 1;
-    const size_t pstride = row * kDpMaxChunks;
-    double v;
-    int a;
-    dp_reduce(at<double>(ws, L.pv) + (keff & 1) * pstride,
-              at<int32_t>(ws, L.pa) + (keff & 1) * pstride, keff, b, v, a);
-    at<double>(ws, L.d)[static_cast<size_t>(keff) * row + b] = v;
-    at<uint16_t>(ws, L.split)[static_cast<size_t>(keff) * row + b] = static_cast<uint16_t>(a);
-}
-
-// Backtracking (one thread): entry j is -1, +1 or the weighted mean of its interval;
-// degenerate histograms (b < k) are padded with +1.
-__global__ void k_dp_backtrack(int32_t nbins, int32_t k, void* ws, double* codebook,
-                               double* cost, int32_t* status)
-{
-    if (threadIdx.x != 0) return;
-    const DpLayout L = dp_layout(nbins, k);
-    const int32_t* hdr = at<int32_t>(ws, L.hdr);
-    const int b = hdr[0];
-    const int keff = hdr[1];
-    const double* Z0 = at<double>(ws, L.z0);
-    const double* Z1 = at<double>(ws, L.z1);
-    const double* cnt = at<double>(ws, L.cnt);
-    const double* ctr = at<double>(ws, L.ctr);
-    const size_t row = static_cast<size_t>(nbins) + 1;
-    const double* D = at<double>(ws, L.d);
-    const uint16_t* split = at<uint16_t>(ws, L.split);
-    if (keff >= 2) {
-        *cost = D[static_cast<size_t>(keff) * row + b];
-        int r = b;
-        for (int j = keff; j >= 1; --j) {
-            const int l = split[static_cast<size_t>(j) * row + r];
-            if (j == 1) {
-                codebook[j - 1] = -1.0;
-            } else if (j == keff) {
-                codebook[j - 1] = 1.0;
-            } else {
-                const double S0 = Z0[r] - Z0[l - 1];
-                const double S1 = Z1[r] - Z1[l - 1];
-                codebook[j - 1] = S1 / S0;
-            }
-            r = l - 1;
-        }
-        for (int j = keff; j < k; ++j) codebook[j] = 1.0;
-    } else {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (keff < 2) {
+        if (tid != 0) return;
+        const double* cnt = at<double>(ws, L.cnt);
+        const double* ctr = at<double>(ws, L.ctr);
         codebook[0] = -1.0;
         for (int j = 1; j < k; ++j) codebook[j] = 1.0;
         double e = 0.0;
@@ -526,50 +591,147 @@ __global__ void k_dp_backtrack(int32_t nbins, int32_t k, void* ws, double* codeb
             e += cnt[i] * d2;
         }
         *cost = e;
+        *status = hdr[2];
+        return;
     }
-    *status = hdr[2];
+    const size_t prev = ((keff - 1) & 1) * row;
+    const double* Dp = at<double>(ws, L.d) + prev;
+    const double zr0 = Z0[b], zr1 = Z1[b], zr2 = Z2[b];
+    double best = INFINITY;
+    int arg = 0x7fffffff;
+    for (int l = keff + tid; l <= b; l += 1024) {   // rising l: the first minimum kept
+        const double c = Dp[l - 1] + dp_cost_forced(1.0, zr0, zr1, zr2, Z0[l - 1], Z1[l - 1],
+                                                    Z2[l - 1]);
+        if (c < best) {
+            best = c;
+            arg = l;
+        }
+    }
+    const double m = wave_min(best);
+    if (best != m) arg = 0x7fffffff;
+    for (int off = 1; off < 64; off <<= 1) {
+        const int o = __shfl_xor(arg, off);
+        arg = o < arg ? o : arg;
+    }
+    if (lane == 0) {
+        sv[wave] = m;
+        sa[wave] = arg;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        double v = sv[0];
+        int a = sa[0];
+        for (int q = 1; q < 16; ++q)
+            if (sv[q] < v || (sv[q] == v && sa[q] < a)) {
+                v = sv[q];
+                a = sa[q];
+            }
+        if (!(v < INFINITY)) a = keff;   // no candidate has a value
+        *cost = v;
+        *status = hdr[2];
+        node[keff] = b;
+        node[keff - 1] = a - 1;
+        // checkpoint levels below keff - 1, multiples of kDpCheck
+        int lev = (keff - 2) / kDpCheck * kDpCheck;
+        if (lev > 0) {
+            int x = at<uint16_t>(ws, L.anc)[prev + a - 1];
+            node[lev] = x;
+            for (; lev > kDpCheck; lev -= kDpCheck) {
+                x = at<uint16_t>(ws, L.jump)[static_cast<size_t>(lev / kDpCheck) * row + x];
+                node[lev - kDpCheck] = x;
+            }
+        }
+        node[0] = 0;
+    }
+    __syncthreads();
+    // stretch s: the levels strictly between checkpoint s and the next one (or keff - 1)
+    const int stretches = (keff - 2) / kDpCheck + 1;
+    if (tid < stretches) {
+        const int base = tid * kDpCheck;
+        int top = base + kDpCheck;
+        if (top > keff - 1) top = keff - 1;
+        int x = node[top];
+        for (int j = top; j > base + 1; --j) {
+            x = at<uint16_t>(ws, L.split)[static_cast<size_t>(j) * row + x] - 1;
+            node[j - 1] = x;
+        }
+    }
+    __syncthreads();
+    for (int j = 1 + tid; j <= k; j += 1024) {
+        double e = 1.0;
+        if (j == 1) {
+            e = -1.0;
+        } else if (j < keff) {
+            const int r = node[j], x = node[j - 1];
+            const double S0 = Z0[r] - Z0[x];
+            const double S1 = Z1[r] - Z1[x];
+            e = S1 / S0;
+        }
+        codebook[j - 1] = e;
+    }
 }
 
 // ---------------------------------------------------------------------------------
 // Codebook installation: fp32 entries, fp64 copy, midpoints and the guide table.
 // guide[bk] = number of midpoints whose bucket is < bk, bucket(x) =
 // min(ng - 1, (int)((x + 1) * ng / 2)) in fp32 -- the same function the step applies
-// to the (clamped) value being encoded, so the lookup is exact for fp32 midpoints.
+// to the (clamped) value being encoded, so the lookup is exact for fp32 midpoints. The
+// midpoints' buckets are counted in LDS and scanned by the workgroup, 16 buckets a thread
+// (85 us with one thread taking the 4096 buckets in turn).
 // ---------------------------------------------------------------------------------
-__global__ void k_install(const double* __restrict__ in64, const float* __restrict__ in32,
-                          int32_t k, int32_t ng, float* cb32, double* cb64, float* mid,
-                          uint8_t* guide)
+constexpr int kGuideRun = kMaxBins / kThreads;   // buckets per thread
+
+__global__ __launch_bounds__(kThreads) void k_install(const double* __restrict__ in64,
+                                                      const float* __restrict__ in32, int32_t k,
+                                                      int32_t ng, float* cb32, double* cb64,
+                                                      float* mid, uint8_t* guide)
 {
     __shared__ float c[kMaxK];
-    __shared__ uint16_t cnt[kMaxBins];
+    __shared__ uint32_t cnt[kMaxBins];
+    __shared__ uint32_t wsum[kThreads / 64];
     const int t = threadIdx.x;
-    for (int i = t; i < k; i += blockDim.x) {
+    for (int i = t; i < k; i += kThreads) {
         const float f = in64 ? static_cast<float>(in64[i]) : in32[i];
         c[i] = f;
         cb32[i] = f;
         cb64[i] = in64 ? in64[i] : static_cast<double>(in32[i]);
     }
-    for (int i = t; i < ng; i += blockDim.x) cnt[i] = 0;
+    for (int i = t; i < kMaxBins; i += kThreads) cnt[i] = 0;
     __syncthreads();
     const float half_ng = 0.5f * static_cast<float>(ng);
-    for (int i = t; i < k; i += blockDim.x) {
+    for (int i = t; i < k; i += kThreads) {
         const float mdp = i + 1 < k ? 0.5f * (c[i] + c[i + 1]) : 2.0f;
         mid[i] = mdp;
-    }
-    if (t == 0) {
-        for (int i = 0; i + 1 < k; ++i) {
-            const float mdp = 0.5f * (c[i] + c[i + 1]);
+        if (i + 1 < k) {
             const float x = fminf(fmaxf(mdp, -1.0f), 1.0f);
             int bk = static_cast<int>((x + 1.0f) * half_ng);
             bk = bk < ng - 1 ? bk : ng - 1;
-            cnt[bk] += 1;
+            atomicAdd(&cnt[bk], 1u);
         }
-        int acc = 0;
-        for (int bk = 0; bk < ng; ++bk) {
-            guide[bk] = static_cast<uint8_t>(acc);
-            acc += cnt[bk];
-        }
-        guide[ng] = static_cast<uint8_t>(acc);
+    }
+    __syncthreads();
+    uint32_t sum = 0;
+#pragma unroll
+    for (int q = 0; q < kGuideRun; ++q) sum += cnt[t * kGuideRun + q];
+    uint32_t acc = sum;
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t up = __shfl_up(acc, off);
+        if ((t & 63) >= off) acc += up;
+    }
+    if ((t & 63) == 63) wsum[t >> 6] = acc;
+    __syncthreads();
+    acc -= sum;
+    for (int w = 0; w < (t >> 6); ++w) acc += wsum[w];
+    // the global guide is padded to 16 bytes past its ng + 1 entries
+    for (int q = 0; q < kGuideRun; ++q) {
+        const int bk = t * kGuideRun + q;
+        if (bk < ng) guide[bk] = static_cast<uint8_t>(acc);
+        acc += cnt[bk];
+    }
+    if (t == 0) {
+        uint32_t all = 0;
+        for (int w = 0; w < kThreads / 64; ++w) all += wsum[w];
+        guide[ng] = static_cast<uint8_t>(all);
         for (int bk = ng + 1; bk < ((ng + 1 + 15) & ~15); ++bk) guide[bk] = 0;
     }
 }
@@ -605,13 +767,14 @@ hipError_t launch_dp(const uint64_t* hist, int32_t nbins, int32_t k, void* ws,
                      hipStream_t stream)
 {
     hipLaunchKernelGGL(k_dp_prep, dim3(1), dim3(kThreads), 0, stream, hist, nbins, k, ws);
-    const dim3 grid((static_cast<unsigned>(nbins) + kDpRows - 1) / kDpRows,
-                    (static_cast<unsigned>(nbins) + kDpChunk - 1) / kDpChunk);
-    for (int j = 1; j <= k; ++j)
-        hipLaunchKernelGGL(k_dp_level, grid, dim3(kDpThreads), 0, stream, nbins, k, j, ws);
-    hipLaunchKernelGGL(k_dp_final, dim3(1), dim3(64), 0, stream, nbins, k, ws);
-    hipLaunchKernelGGL(k_dp_backtrack, dim3(1), dim3(64), 0, stream, nbins, k, ws,
-                       codebook_out, cost_out, status_out);
+    for (int j = 2; j < k; ++j) {
+        // rows j .. nbins - k + j at most (b <= nbins, keff <= k; with b < k: rows j .. j)
+        const int rows = nbins > k ? nbins - k + 1 : 1;
+        hipLaunchKernelGGL(k_dp_level, dim3((rows + kDpRows - 1) / kDpRows), dim3(kDpThreads), 0,
+                           stream, nbins, k, j, ws);
+    }
+    hipLaunchKernelGGL(k_dp_last, dim3(1), dim3(1024), 0, stream, nbins, k, ws, codebook_out,
+                       cost_out, status_out);
     return hipGetLastError();
 }
 
