@@ -44,25 +44,9 @@ int fail(int code, const char* fmt, ...)
 using Class = PlanClass;
 
 constexpr int kSegSlots = 4;                 // device tensor tables cached per state
-constexpr int64_t kPartChunk = 65536;     // elements of one partition sub-chunk (mode 1)
-constexpr int64_t kPartItemElems = 16384; // elements per partition item (mode 0)
-constexpr int kPartMaxPairs = 2048;
 constexpr uint32_t kCkptMagic = 0x4e464547u;   // "GEFN"
 
 hipStream_t as_stream(void* s) { return static_cast<hipStream_t>(s); }
-
-std::vector<int64_t> divisors_of(int64_t n)
-{
-    std::vector<int64_t> lo, hi;
-    for (int64_t d = 1; d <= n / d; ++d) {
-        if (n % d == 0) {
-            lo.push_back(d);
-            if (d != n / d) hi.push_back(n / d);
-        }
-    }
-    for (auto it = hi.rbegin(); it != hi.rend(); ++it) lo.push_back(*it);
-    return lo;
-}
 
 bool finite_f(double x) { return std::isfinite(x); }
 
@@ -343,97 +327,93 @@ int plan_tiles(gefen_state* st, const std::vector<std::vector<int64_t>>& starts)
 }
 
 // Alg. 2 for a list of tensors. Writes one period per tensor (host), and optionally the
-// scores of every divisor (host, concatenated in tensor order).
+// divisors and their scores (host, concatenated in tensor order). Tables, sums and results
+// share one device allocation.
 int infer_periods(const std::vector<gefen_tensor>& ts, double eps, hipStream_t stream,
                   std::vector<int64_t>& periods, std::vector<int64_t>* divs_out,
                   std::vector<double>* scores_out)
 {
-    std::vector<PartDesc> descs;
-    std::vector<int32_t> first, count;
-    std::vector<int64_t> all_divs;
-    int64_t items = 0, slots = 0;
-    for (const gefen_tensor& g : ts) {
-        const int64_t n = g.numel;
-        const std::vector<int64_t> dv = divisors_of(n);
-        first.push_back(static_cast<int32_t>(descs.size()));
-        count.push_back(static_cast<int32_t>(dv.size()));
-        for (int64_t p : dv) {
-            PartDesc d{};
-            d.grad = g.ptr;
-            d.n = n;
-            d.p = p;
-            d.gdtype = g.dtype;
-            d.item0 = items;
-            d.out0 = slots;
-            const int64_t nb = n / p;
-            if (nb < 2) {
-                d.mode = 0;
-                d.rpi = 1;
-                d.n_items = 0;
-            } else if (p <= kPartChunk) {
-                d.mode = 0;
-                int64_t rpi = kPartItemElems / p;
-                rpi = std::max<int64_t>(1, std::min<int64_t>(rpi, kPartMaxPairs));
-                d.rpi = static_cast<int32_t>(rpi);
-                d.n_items = (nb - 1 + rpi - 1) / rpi;
-                slots += d.n_items;
-            } else {
-                d.mode = 1;
-                d.rpi = static_cast<int32_t>((p + kPartChunk - 1) / kPartChunk);
-                d.n_items = nb * d.rpi;
-                slots += d.n_items;
-            }
-            items += d.n_items;
-            descs.push_back(d);
-            all_divs.push_back(p);
-        }
-    }
-    const int32_t nd = static_cast<int32_t>(descs.size());
-    const int32_t nt = static_cast<int32_t>(ts.size());
-    void *d_descs = nullptr, *d_partials = nullptr, *d_scores = nullptr, *d_first = nullptr,
-         *d_count = nullptr, *d_periods = nullptr;
-    auto cleanup = [&]() {
-        for (void* p : {d_descs, d_partials, d_scores, d_first, d_count, d_periods})
-            if (p) (void)hipFree(p);
+    PartPlan plan;
+    int64_t total = 0;
+    for (const gefen_tensor& g : ts) total += g.numel;
+    for (const gefen_tensor& g : ts) part_add(plan, g.ptr, g.numel, g.dtype, total);
+    part_finish(plan);
+    const size_t ns = plan.scores.size(), nt = ts.size();
+    size_t bytes = 0;
+    auto room = [&](size_t b) {
+        const size_t at = bytes;
+        bytes += (b + 255) / 256 * 256;
+        return at;
     };
-#define GEFEN_PART_HIP(call)                                                             \
-    do {                                                                                 \
-        hipError_t e_ = (call);                                                          \
-        if (e_ != hipSuccess) {                                                          \
-            cleanup();                                                                   \
-            return fail(GEFEN_EHIP, "%s failed: %s", #call, hipGetErrorString(e_));      \
-        }                                                                                \
-    } while (0)
-    GEFEN_PART_HIP(hipMalloc(&d_descs, sizeof(PartDesc) * std::max(nd, 1)));
-    GEFEN_PART_HIP(hipMalloc(&d_partials, sizeof(double) * std::max<int64_t>(slots, 1)));
-    GEFEN_PART_HIP(hipMalloc(&d_scores, sizeof(double) * std::max(nd, 1)));
-    GEFEN_PART_HIP(hipMalloc(&d_first, sizeof(int32_t) * std::max(nt, 1)));
-    GEFEN_PART_HIP(hipMalloc(&d_count, sizeof(int32_t) * std::max(nt, 1)));
-    GEFEN_PART_HIP(hipMalloc(&d_periods, sizeof(int64_t) * std::max(nt, 1)));
-    GEFEN_PART_HIP(hipMemcpyAsync(d_descs, descs.data(), sizeof(PartDesc) * nd,
-                                  hipMemcpyHostToDevice, stream));
-    GEFEN_PART_HIP(hipMemcpyAsync(d_first, first.data(), sizeof(int32_t) * nt,
-                                  hipMemcpyHostToDevice, stream));
-    GEFEN_PART_HIP(hipMemcpyAsync(d_count, count.data(), sizeof(int32_t) * nt,
-                                  hipMemcpyHostToDevice, stream));
-    GEFEN_PART_HIP(launch_partition(static_cast<PartDesc*>(d_descs), nd, items, eps,
-                                    static_cast<double*>(d_partials),
-                                    static_cast<double*>(d_scores),
-                                    static_cast<int32_t*>(d_first),
-                                    static_cast<int32_t*>(d_count), nt,
-                                    static_cast<int64_t*>(d_periods), stream));
-    periods.assign(nt, 1);
-    GEFEN_PART_HIP(hipMemcpyAsync(periods.data(), d_periods, sizeof(int64_t) * nt,
-                                  hipMemcpyDeviceToHost, stream));
-    if (scores_out) {
-        scores_out->assign(nd, 0.0);
-        GEFEN_PART_HIP(hipMemcpyAsync(scores_out->data(), d_scores, sizeof(double) * nd,
-                                      hipMemcpyDeviceToHost, stream));
+    // the tables, copied from one host image
+    size_t n_jobs = 0;
+    for (const auto& l : plan.launches) n_jobs += l.size();
+    const size_t o_tensors = room(sizeof(PartTensor) * nt);
+    const size_t o_units = room(sizeof(PartUnit) * plan.units.size());
+    const size_t o_phase = room(sizeof(int32_t) * plan.phase_end.size());
+    const size_t o_keep = room(sizeof(int64_t) * plan.keep.size());
+    const size_t o_jobs = room(sizeof(PartJob) * n_jobs);
+    const size_t o_scores = room(sizeof(PartScore) * ns);
+    const size_t o_first = room(sizeof(int32_t) * nt);
+    const size_t o_count = room(sizeof(int32_t) * nt);
+    std::vector<char> image(bytes);
+    std::memcpy(&image[o_tensors], plan.tensors.data(), sizeof(PartTensor) * nt);
+    std::memcpy(image.data() + o_units, plan.units.data(), sizeof(PartUnit) * plan.units.size());
+    std::memcpy(image.data() + o_phase, plan.phase_end.data(),
+                sizeof(int32_t) * plan.phase_end.size());
+    std::memcpy(image.data() + o_keep, plan.keep.data(), sizeof(int64_t) * plan.keep.size());
+    size_t at = o_jobs;
+    for (const auto& l : plan.launches) {
+        std::memcpy(image.data() + at, l.data(), sizeof(PartJob) * l.size());
+        at += sizeof(PartJob) * l.size();
     }
-    GEFEN_PART_HIP(hipStreamSynchronize(stream));
-#undef GEFEN_PART_HIP
-    cleanup();
-    if (divs_out) *divs_out = all_divs;
+    std::memcpy(&image[o_scores], plan.scores.data(), sizeof(PartScore) * ns);
+    std::memcpy(&image[o_first], plan.first.data(), sizeof(int32_t) * nt);
+    std::memcpy(&image[o_count], plan.count.data(), sizeof(int32_t) * nt);
+    // results, then sums and partial contrasts
+    const size_t o_periods = room(sizeof(int64_t) * nt);
+    const size_t o_values = room(sizeof(double) * ns);
+    const size_t results = bytes - o_periods;
+    const size_t o_sums = room(sizeof(double) * static_cast<size_t>(plan.sums));
+    const size_t o_part = room(sizeof(double) * static_cast<size_t>(plan.parts));
+    char* dev = nullptr;
+    GEFEN_HIP(hipMalloc(reinterpret_cast<void**>(&dev), bytes));
+    std::vector<char> host(results);
+    auto run = [&]() -> int {
+        GEFEN_HIP(hipMemcpyAsync(dev, image.data(), image.size(), hipMemcpyHostToDevice, stream));
+        PartDevice d{};
+        d.tensors = reinterpret_cast<PartTensor*>(dev + o_tensors);
+        d.units = reinterpret_cast<PartUnit*>(dev + o_units);
+        d.phase_end = reinterpret_cast<int32_t*>(dev + o_phase);
+        d.keep = reinterpret_cast<int64_t*>(dev + o_keep);
+        d.jobs = reinterpret_cast<PartJob*>(dev + o_jobs);
+        d.scores = reinterpret_cast<PartScore*>(dev + o_scores);
+        d.first = reinterpret_cast<int32_t*>(dev + o_first);
+        d.count = reinterpret_cast<int32_t*>(dev + o_count);
+        d.periods = reinterpret_cast<int64_t*>(dev + o_periods);
+        d.values = reinterpret_cast<double*>(dev + o_values);
+        d.sums = reinterpret_cast<double*>(dev + o_sums);
+        d.part = reinterpret_cast<double*>(dev + o_part);
+        GEFEN_HIP(launch_partition(plan, d, eps, stream));
+        GEFEN_HIP(hipMemcpyAsync(host.data(), dev + o_periods, results, hipMemcpyDeviceToHost,
+                                 stream));
+        GEFEN_HIP(hipStreamSynchronize(stream));
+        return GEFEN_OK;
+    };
+    const int rc = run();
+    if (rc) (void)hipStreamSynchronize(stream);   // nothing may still read the host image
+    (void)hipFree(dev);
+    if (rc) return rc;
+    periods.resize(nt);
+    std::memcpy(periods.data(), host.data(), sizeof(int64_t) * nt);
+    if (scores_out) {
+        scores_out->resize(ns);
+        std::memcpy(scores_out->data(), host.data() + (o_values - o_periods), sizeof(double) * ns);
+    }
+    if (divs_out) {
+        divs_out->clear();
+        for (const PartScore& s : plan.scores) divs_out->push_back(s.p);
+    }
     return GEFEN_OK;
 }
 

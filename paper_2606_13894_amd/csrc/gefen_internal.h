@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "part_plan.h"
 #include "tile_plan.h"
 
 namespace gefen {
@@ -108,22 +109,20 @@ hipError_t launch_install_codebook_f32(const float* cb32_in, int32_t k, int32_t 
                                        float* cb32, double* cb64, float* mid,
                                        uint8_t* guide, hipStream_t stream);
 
-// Block partitioning (Alg. 2) of several tensors.
-struct PartDesc {              // one (tensor, divisor) pair
-    const void* grad;
-    int64_t n;                 // tensor numel
-    int64_t p;                 // divisor
-    int64_t item0;             // first work item of this pair
-    int64_t n_items;           // work items of this pair
-    int64_t out0;              // first partial-output slot
-    int32_t gdtype;
-    int32_t mode;              // 0: pairs of block means per item; 1: sub-chunk sums
-    int32_t rpi;               // mode 0: block pairs per item; mode 1: sub-chunks per block
-    int32_t pad;
+// Block partitioning (Alg. 2) of several tensors: the plan's tables, sums, partial contrasts,
+// scores (one double each) and periods on the device.
+struct PartDevice {
+    const PartTensor* tensors;
+    const PartUnit* units;
+    const int32_t* phase_end;
+    const int64_t* keep;
+    const PartJob* jobs;          // the launches' jobs one after another
+    const PartScore* scores;
+    const int32_t *first, *count;
+    double *sums, *part, *values;
+    int64_t* periods;
 };
-hipError_t launch_partition(const PartDesc* descs, int32_t n_desc, int64_t n_items,
-                            double eps, double* partials, double* scores,
-                            const int32_t* tensor_first_desc, const int32_t* tensor_n_desc,
-                            int32_t n_tensors, int64_t* periods, hipStream_t stream);
+hipError_t launch_partition(const PartPlan& plan, const PartDevice& d, double eps,
+                            hipStream_t stream);
 
 }  // namespace gefen

@@ -7,13 +7,12 @@
 // then the strict local maxima of S over the sorted divisors (1 < p < n), and the one
 // with the largest S (ties: smallest p), else 1.
 //
-// Work items (one workgroup each) are described per (tensor, divisor) pair:
-//   mode 0 (p <= kPBig): an item owns `rpi` consecutive pairs of blocks; it computes the
-//          means of the rpi + 1 blocks involved (the last one is recomputed by the next
-//          item) and writes the item's sum of |mu_{i+1} - mu_i|.
-//   mode 1 (p >  kPBig): an item sums z over one sub-chunk of kChunk elements of one
-//          block; the finalize kernel assembles block means from the sub-chunk sums.
-// All sums run in a fixed order, so the scores are deterministic.
+// The sums are built from each other (part_plan.h): one pass over the gradient with one
+// float64 logarithm per element forms those of every divisor of L in LDS, and the other
+// divisors' sums come from stored ones. Evaluating z once per divisor, as the definition
+// reads, took 32.5 ms on the GPT-2 small shapes and 235 ms on the Llama-3 1.5B shapes; see
+// launch_partition for this form. All sums run in a fixed order (the same tree for every
+// block of one divisor), so the scores are deterministic.
 #include "gefen_internal.h"
 
 #include <math.h>
@@ -21,8 +20,7 @@
 namespace gefen {
 namespace {
 
-constexpr int64_t kChunk = 65536;
-constexpr int kMaxPairs = 2048;
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ double z_at(const void* g, int gdt, int64_t i, double eps)
 {
@@ -54,143 +52,311 @@ __device__ __forceinline__ double block_sum(double v, double* red)
     return t;
 }
 
-__device__ __forceinline__ int find_desc(const PartDesc* descs, int32_t n_desc, int64_t item)
+// The last of `n` records (by their first item) whose first item is at most `item`.
+template <typename T, typename F>
+__device__ __forceinline__ int find_item(const T* recs, int32_t n, int64_t item, F first)
 {
-    int lo = 0, hi = n_desc - 1;
+    int lo = 0, hi = n - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        if (descs[mid].item0 <= item) lo = mid; else hi = mid - 1;
+        if (first(recs[mid]) <= item) lo = mid; else hi = mid - 1;
     }
     return lo;
 }
 
-__global__ __launch_bounds__(kThreads) void k_part_items(const PartDesc* __restrict__ descs,
-                                                         int32_t n_desc, double eps,
-                                                         double* __restrict__ partials)
+// A wave's sum by lane permutes inside the vector unit, in every lane of the result's row
+// and complete in lane 63 (quads, rows of 16, then the rows in order).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double v)
 {
-    __shared__ double mu[kMaxPairs + 1];
+    const uint64_t x = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(x), CTRL, ROWS, 0xf, false);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(x >> 32), CTRL, ROWS, 0xf,
+                                                    false);
+    return v + __builtin_bit_cast(double, (static_cast<uint64_t>(hi) << 32) | lo);
+}
+
+__device__ __forceinline__ double wave_sum63(double v)
+{
+    v = dpp_add<0xB1, 0xf>(v);    // quad_perm 1,0,3,2
+    v = dpp_add<0x4E, 0xf>(v);    // quad_perm 2,3,0,1
+    v = dpp_add<0x141, 0xf>(v);   // row_half_mirror
+    v = dpp_add<0x140, 0xf>(v);   // row_mirror
+    v = dpp_add<0x142, 0xa>(v);   // row_bcast15 into rows 1 and 3
+    return dpp_add<0x143, 0xc>(v);   // row_bcast31 into rows 2 and 3
+}
+
+// The base pass. About 40 float64 operations for each logarithm against 2 to 4 bytes; the
+// sums of all divisors of L add about two LDS reads and an addition per element. What bounds
+// it is the chain of phases, so a chunk is small (five or more 256-thread workgroups a CU
+// hide each other's barriers), the waves of a phase work on different divisors, the units'
+// descriptors lie in LDS with the next one loaded ahead, and a workgroup takes a run of
+// chunks: the search for its tensor is paid once, the next chunk's gradients are loaded
+// under the work on this one, and contrasts add up over the run. On the GPT-2 small shapes:
+// 2.09 ms with one 2048-element chunk per workgroup and all its threads on one divisor at a
+// time; this: see launch_partition.
+__global__ __launch_bounds__(kPartThreads) void k_part_base(const PartTensor* __restrict__ tensors,
+                                                            int32_t n_tensors,
+                                                            const PartUnit* __restrict__ units,
+                                                            const int32_t* __restrict__ phase_end,
+                                                            const int64_t* __restrict__ keep,
+                                                            double eps, double* __restrict__ sums,
+                                                            double* __restrict__ part)
+{
+    extern __shared__ double S[];
+    __shared__ u32x4 un[kPartMaxUnit];
+    __shared__ int pe[kPartMaxPhase];
+    __shared__ double gap[kPartMaxUnit];      // contrasts of the run, by GAP unit
+    __shared__ double edge[kPartMaxEntry];    // last sum of the chunk before, by entry
+    const int64_t item = blockIdx.x;
+    const PartTensor t = tensors[find_item(tensors, n_tensors, item,
+                                           [](const PartTensor& x) { return x.group0; })];
+    const int64_t grp = item - t.group0;
+    const int64_t c0 = grp * t.run;
+    const int64_t c1 = c0 + t.run < t.nchunk ? c0 + t.run : t.nchunk;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    constexpr int kPer = kPartChunkMax / kPartThreads;
+    float g[kPer];
+    auto load = [&](int64_t c) {   // elements past the tensor read its last one
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            int64_t i = c * t.chunk + tid + u * kPartThreads;
+            i = i < t.n ? i : t.n - 1;
+            if (t.gdtype == DT_F32)
+                g[u] = static_cast<const float*>(t.grad)[i];
+            else
+                g[u] = __uint_as_float(
+                    static_cast<uint32_t>(static_cast<const uint16_t*>(t.grad)[i]) << 16);
+        }
+    };
+    load(c0);
+    for (int u = tid; u < t.nunit; u += kPartThreads) {
+        un[u] = reinterpret_cast<const u32x4*>(units + t.unit0)[u];
+        gap[u] = 0.0;
+    }
+    if (tid < t.nphase) pe[tid] = phase_end[t.phase0 + tid];
+    for (int64_t c = c0; c < c1; ++c) {
+        const int64_t start = c * t.chunk;
+        const int len = static_cast<int>(t.n - start < t.chunk ? t.n - start : t.chunk);
+        const bool whole = len == t.chunk;
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const int i = tid + u * kPartThreads;
+            const double x = static_cast<double>(g[u]);
+            if (i < len) S[i] = log(x * x + eps);   // p = 1 lies at 0
+        }
+        if (c + 1 < c1) load(c + 1);
+        int u = wave;
+        __syncthreads();
+        for (int f = 1; f < t.nphase; ++f) {
+            const int end = pe[f];
+            u32x4 next = un[u < end ? u : 0];
+            while (u < end) {
+                const u32x4 w = next;
+                const int u1 = u + kPartThreads / 64;
+                next = un[u1 < end ? u1 : u];
+                const uint32_t w0 = __builtin_amdgcn_readfirstlane(static_cast<int>(w.x));
+                const uint32_t w1 = __builtin_amdgcn_readfirstlane(static_cast<int>(w.y));
+                const uint32_t w2 = __builtin_amdgcn_readfirstlane(static_cast<int>(w.z));
+                const uint32_t w3 = __builtin_amdgcn_readfirstlane(static_cast<int>(w.w));
+                const int kind = w0 & 0xffff, p = w0 >> 16, q = w1 & 0xffff;
+                const int i0 = w2 >> 16, slot = w3 >> 16;
+                const int cnt = whole ? static_cast<int>(w3 & 0xffff) : len / p;
+                const double* __restrict__ s = S + (w1 >> 16);
+                const int stop = i0 + kPartUnit < cnt ? i0 + kPartUnit : cnt;
+                if (kind == PART_ADD) {
+                    double* __restrict__ d = S + (w2 & 0xffff);
+                    if (q == 2) {
+#pragma unroll 4
+                        for (int i = i0 + lane; i < stop; i += 64) d[i] = s[2 * i] + s[2 * i + 1];
+                    } else if (q == 3) {
+#pragma unroll 4
+                        for (int i = i0 + lane; i < stop; i += 64)
+                            d[i] = s[3 * i] + s[3 * i + 1] + s[3 * i + 2];
+                    } else {
+                        for (int i = i0 + lane; i < stop; i += 64) {
+                            double a = s[i * q];
+#pragma unroll 4
+                            for (int j = 1; j < q; ++j) a += s[i * q + j];
+                            d[i] = a;
+                        }
+                    }
+                } else if (kind == PART_GAP) {
+                    const int top = stop < cnt ? stop : cnt - 1;
+                    double acc = 0.0;
+#pragma unroll 4
+                    for (int i = i0 + lane; i < top; i += 64) acc += fabs(s[i + 1] - s[i]);
+                    acc = wave_sum63(acc);
+                    if (lane == 63) {   // the unit is this wave's in every chunk
+                        const int e = w2 & 0xffff;
+                        if (i0 == 0) {
+                            double* __restrict__ o = part + t.out0 + (t.ngap + e) * t.ngroup + grp;
+                            if (c == c0)
+                                o[0] = s[0];
+                            else
+                                acc += fabs(s[0] - edge[e]);
+                            edge[e] = s[cnt - 1];
+                            if (c + 1 == c1) o[t.nentry * t.ngroup] = s[cnt - 1];
+                        }
+                        const double sum = gap[slot] + acc;
+                        gap[slot] = sum;
+                        if (c + 1 == c1) part[t.out0 + slot * t.ngroup + grp] = sum;
+                    }
+                } else {
+                    double* __restrict__ o = sums + keep[t.keep0 + slot] + start / p;
+                    for (int i = i0 + lane; i < stop; i += 64) o[i] = s[i];
+                }
+                u = u1;
+            }
+            u = end + wave;
+            __syncthreads();
+        }
+    }
+}
+
+// Terms [a, b) of a job's source, summed by `stride` threads of which this is `tid`.
+__device__ __forceinline__ double term_sum(const PartJob& j, const PartTensor& t,
+                                           const double* __restrict__ sums, double eps, int64_t a,
+                                           int64_t b, int tid, int stride)
+{
+    double acc = 0.0;
+    if (j.src >= 0) {
+        const double* __restrict__ s = sums + j.src;
+        for (int64_t i = a + tid; i < b; i += stride) acc += s[i];
+    } else {
+        for (int64_t i = a + tid; i < b; i += stride) acc += z_at(t.grad, t.gdtype, i, eps);
+    }
+    return acc;
+}
+
+__global__ __launch_bounds__(kThreads) void k_part_jobs(const PartJob* __restrict__ jobs,
+                                                        int32_t n_jobs,
+                                                        const PartTensor* __restrict__ tensors,
+                                                        double eps, double* __restrict__ sums,
+                                                        double* __restrict__ part)
+{
     __shared__ double red[kThreads / 64];
     const int64_t item = blockIdx.x;
-    const PartDesc d = descs[find_desc(descs, n_desc, item)];
-    const int64_t it = item - d.item0;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = tid >> 6;
-    const int64_t p = d.p;
-
-    if (d.mode == 1) {
-        const int64_t blk = it / d.rpi;
-        const int64_t c = it % d.rpi;
-        const int64_t start = blk * p + c * kChunk;
-        const int64_t stop = start + kChunk < (blk + 1) * p ? start + kChunk : (blk + 1) * p;
+    const PartJob j = jobs[find_item(jobs, n_jobs, item, [](const PartJob& x) { return x.item0; })];
+    const PartTensor t = tensors[j.tensor];
+    const int64_t it = item - j.item0;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (j.kind == PART_DIFF) {
+        const double* __restrict__ s = sums + j.src;
+        const int64_t a = it * j.per;
+        const int64_t b = a + j.per < j.count - 1 ? a + j.per : j.count - 1;
         double acc = 0.0;
-        for (int64_t i = start + tid; i < stop; i += kThreads) acc += z_at(d.grad, d.gdtype, i, eps);
-        const double t = block_sum(acc, red);
-        if (tid == 0) partials[d.out0 + it] = t;
+        for (int64_t i = a + tid; i < b; i += kThreads) acc += fabs(s[i + 1] - s[i]);
+        acc = block_sum(acc, red);
+        if (tid == 0) part[j.dst + it] = acc;
         return;
     }
-
-    const int64_t nb = d.n / p;
-    const int64_t b0 = it * d.rpi;
-    const int64_t npairs = (b0 + d.rpi < nb - 1 ? b0 + d.rpi : nb - 1) - b0;
-    const int nbk = static_cast<int>(npairs) + 1;
-    const double inv_p_den = static_cast<double>(p);
-    if (p <= 16) {
-        for (int i = tid; i < nbk; i += kThreads) {
-            const int64_t s0 = (b0 + i) * p;
-            double acc = 0.0;
-            for (int64_t e = 0; e < p; ++e) acc += z_at(d.grad, d.gdtype, s0 + e, eps);
-            mu[i] = acc / inv_p_den;
-        }
-    } else {
-        for (int i = wave; i < nbk; i += kThreads / 64) {
-            const int64_t s0 = (b0 + i) * p;
-            double acc = 0.0;
-            for (int64_t e = lane; e < p; e += 64) acc += z_at(d.grad, d.gdtype, s0 + e, eps);
-            acc = wave_sum(acc);
-            if (lane == 0) mu[i] = acc / inv_p_den;
+    if (j.kind == PART_SUB) {
+        const int64_t blk = it / j.sub, a = blk * j.q + (it % j.sub) * kPartSub;
+        const int64_t end = (blk + 1) * j.q;
+        const double s = block_sum(term_sum(j, t, sums, eps, a, a + kPartSub < end ? a + kPartSub
+                                                                                  : end,
+                                            tid, kThreads), red);
+        if (tid == 0) sums[j.dst + it] = s;
+        return;
+    }
+    const int64_t b0 = it * j.per;
+    const int64_t b1 = b0 + j.per < j.count ? b0 + j.per : j.count;
+    if (j.per == 1) {          // long blocks: the workgroup
+        const double s = block_sum(term_sum(j, t, sums, eps, b0 * j.q, (b0 + 1) * j.q, tid, kThreads),
+                                   red);
+        if (tid == 0) sums[j.dst + b0] = s;
+    } else if (j.q <= 16) {    // short ones: a thread each
+        for (int64_t b = b0 + tid; b < b1; b += kThreads)
+            sums[j.dst + b] = term_sum(j, t, sums, eps, b * j.q, (b + 1) * j.q, 0, 1);
+    } else {                   // a wave each
+        for (int64_t b = b0 + wave; b < b1; b += kThreads / 64) {
+            const double s = wave_sum(term_sum(j, t, sums, eps, b * j.q, (b + 1) * j.q, lane, 64));
+            if (lane == 0) sums[j.dst + b] = s;
         }
     }
-    __syncthreads();
-    double acc = 0.0;
-    for (int i = tid; i < npairs; i += kThreads) acc += fabs(mu[i + 1] - mu[i]);
-    const double t = block_sum(acc, red);
-    if (tid == 0) partials[d.out0 + it] = t;
 }
 
-__global__ __launch_bounds__(kThreads) void k_part_finalize(const PartDesc* __restrict__ descs,
-                                                            const double* __restrict__ partials,
-                                                            double* __restrict__ scores)
+__global__ __launch_bounds__(kThreads) void k_part_finalize(const PartScore* __restrict__ scores,
+                                                            const double* __restrict__ part,
+                                                            double* __restrict__ out)
 {
     __shared__ double red[kThreads / 64];
-    const PartDesc d = descs[blockIdx.x];
+    const PartScore s = scores[blockIdx.x];
     const int tid = threadIdx.x;
-    const int64_t nb = d.n / d.p;
-    if (nb < 2) {
-        if (tid == 0) scores[blockIdx.x] = 0.0;
+    if (s.nb < 2) {
+        if (tid == 0) out[blockIdx.x] = 0.0;
         return;
     }
+    const double* __restrict__ x = part + s.out;
     double acc = 0.0;
-    if (d.mode == 0) {
-        for (int64_t i = tid; i < d.n_items; i += kThreads) acc += partials[d.out0 + i];
-    } else {
-        // block means from sub-chunk sums (in chunk order), then adjacent contrasts
-        const double pd = static_cast<double>(d.p);
-        for (int64_t i = tid; i + 1 < nb; i += kThreads) {
-            double s0 = 0.0, s1 = 0.0;
-            for (int c = 0; c < d.rpi; ++c) s0 += partials[d.out0 + i * d.rpi + c];
-            for (int c = 0; c < d.rpi; ++c) s1 += partials[d.out0 + (i + 1) * d.rpi + c];
-            acc += fabs(s1 / pd - s0 / pd);
-        }
-    }
+#pragma unroll 4
+    for (int64_t i = tid; i < s.terms; i += kThreads) acc += x[i];
+    const double* __restrict__ f = part + s.firsts;
+    const double* __restrict__ l = part + s.lasts;
+#pragma unroll 4
+    for (int64_t i = tid; i + 1 < s.runs; i += kThreads) acc += fabs(f[i + 1] - l[i]);
     const double t = block_sum(acc, red);
-    if (tid == 0) scores[blockIdx.x] = t / static_cast<double>(nb - 1);
+    if (tid == 0) out[blockIdx.x] = t / static_cast<double>(s.p) / static_cast<double>(s.nb - 1);
 }
 
-// Strict local maxima over the sorted divisor list (1 and n included as neighbours),
-// then the largest score (first on ties), else period 1.
-__global__ void k_part_select(const PartDesc* __restrict__ descs,
-                              const double* __restrict__ scores,
-                              const int32_t* __restrict__ first, const int32_t* __restrict__ count,
-                              int32_t n_tensors, int64_t* __restrict__ periods)
+// Strict local maxima over the sorted divisor list (1 and n included as neighbours), then
+// the largest score (first on ties), else period 1. One wave per tensor.
+__global__ __launch_bounds__(64) void k_part_select(const PartScore* __restrict__ divs,
+                                                    const double* __restrict__ scores,
+                                                    const int32_t* __restrict__ first,
+                                                    const int32_t* __restrict__ count,
+                                                    int64_t* __restrict__ periods)
 {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n_tensors) return;
+    const int t = blockIdx.x, lane = threadIdx.x;
     const int f = first[t];
     const int c = count[t];
-    int64_t best = 1;
+    int best = 0x7fffffff;   // index of the lane's best maximum
     double best_s = 0.0;
-    bool have = false;
-    for (int i = 1; i + 1 < c; ++i) {
+    for (int i = 1 + lane; i + 1 < c; i += 64) {
         const double s = scores[f + i];
-        if (s > scores[f + i - 1] && s > scores[f + i + 1]) {
-            if (!have || s > best_s) {
-                best = descs[f + i].p;
-                best_s = s;
-                have = true;
-            }
+        if (s > scores[f + i - 1] && s > scores[f + i + 1] && (best == 0x7fffffff || s > best_s)) {
+            best = i;
+            best_s = s;
         }
     }
-    periods[t] = best;
+    for (int off = 1; off < 64; off <<= 1) {
+        const int ob = __shfl_xor(best, off);
+        const double os = __shfl_xor(best_s, off);
+        if (ob != 0x7fffffff && (best == 0x7fffffff || os > best_s || (os == best_s && ob < best))) {
+            best = ob;
+            best_s = os;
+        }
+    }
+    if (lane == 0) periods[t] = best == 0x7fffffff ? 1 : divs[f + best].p;
 }
 
 }  // namespace
 
-hipError_t launch_partition(const PartDesc* descs, int32_t n_desc, int64_t n_items, double eps,
-                            double* partials, double* scores, const int32_t* tensor_first_desc,
-                            const int32_t* tensor_n_desc, int32_t n_tensors, int64_t* periods,
+hipError_t launch_partition(const PartPlan& plan, const PartDevice& d, double eps,
                             hipStream_t stream)
 {
-    if (n_items > 0x7fffffffLL) return hipErrorInvalidValue;
-    if (n_items > 0)
-        hipLaunchKernelGGL(k_part_items, dim3(static_cast<unsigned>(n_items)), dim3(kThreads), 0,
-                           stream, descs, n_desc, eps, partials);
-    if (n_desc > 0)
-        hipLaunchKernelGGL(k_part_finalize, dim3(static_cast<unsigned>(n_desc)), dim3(kThreads),
-                           0, stream, descs, partials, scores);
-    if (n_tensors > 0)
-        hipLaunchKernelGGL(k_part_select, dim3((n_tensors + 63) / 64), dim3(64), 0, stream,
-                           descs, scores, tensor_first_desc, tensor_n_desc, n_tensors, periods);
+    const int32_t nt = static_cast<int32_t>(plan.tensors.size());
+    const int32_t ns = static_cast<int32_t>(plan.scores.size());
+    if (plan.groups > 0x7fffffffLL) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_part_base, dim3(static_cast<unsigned>(plan.groups)), dim3(kPartThreads),
+                       sizeof(double) * plan.lds_doubles, stream, d.tensors, nt, d.units,
+                       d.phase_end, d.keep, eps, d.sums, d.part);
+    const PartJob* jobs = d.jobs;
+    for (const std::vector<PartJob>& l : plan.launches) {
+        if (l.empty()) continue;
+        const int64_t items = l.back().item0 + l.back().n_items;
+        if (items > 0x7fffffffLL) return hipErrorInvalidValue;
+        hipLaunchKernelGGL(k_part_jobs, dim3(static_cast<unsigned>(items)), dim3(kThreads), 0,
+                           stream, jobs, static_cast<int32_t>(l.size()), d.tensors, eps, d.sums,
+                           d.part);
+        jobs += l.size();
+    }
+    hipLaunchKernelGGL(k_part_finalize, dim3(static_cast<unsigned>(ns)), dim3(kThreads), 0, stream,
+                       d.scores, d.part, d.values);
+    hipLaunchKernelGGL(k_part_select, dim3(static_cast<unsigned>(nt)), dim3(64), 0, stream, d.scores,
+                       d.values, d.first, d.count, d.periods);
     return hipGetLastError();
 }
 
