@@ -26,11 +26,6 @@ __device__ __forceinline__ float grad_at(const Seg& sg, int64_t i)
     return __uint_as_float(static_cast<uint32_t>(static_cast<const uint16_t*>(sg.grad)[i]) << 16);
 }
 
-__device__ __forceinline__ int bin_of(float g, float a, double half_nb, int nbins)
-{
-    return hist_bin(g, a, half_nb, nbins);
-}
-
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
@@ -92,19 +87,20 @@ __device__ __forceinline__ float span_absmax(const Seg& sg, const GSpan& sp, int
     return a;
 }
 
-__device__ __forceinline__ void span_bins(const Seg& sg, const GSpan& sp, float a, double half_nb,
-                                          int nbins, uint32_t* h, int tid, int stride)
+__device__ __forceinline__ void span_bins(const Seg& sg, const GSpan& sp, float absmax,
+                                          double half_nb, int nbins, uint32_t* h, int tid, int stride)
 {
+    const HistBlock a = hist_block(absmax);
 #pragma unroll 2
     for (int64_t v = sp.vb + tid; v < sp.ve; v += stride) {
         float g[4];
         grad4_at(sg, v, g);
 #pragma unroll
-        for (int c = 0; c < 4; ++c) atomicAdd(&h[bin_of(g[c], a, half_nb, nbins)], 1u);
+        for (int c = 0; c < 4; ++c) atomicAdd(&h[hist_bin(g[c], a, half_nb, nbins)], 1u);
     }
     for (int64_t i = tid; i < sp.nh + sp.nt; i += stride) {
         const int64_t e = i < sp.nh ? sp.start + i : sp.tail0 + (i - sp.nh);
-        atomicAdd(&h[bin_of(grad_at(sg, e), a, half_nb, nbins)], 1u);
+        atomicAdd(&h[hist_bin(grad_at(sg, e), a, half_nb, nbins)], 1u);
     }
 }
 
@@ -119,6 +115,173 @@ __device__ __forceinline__ void tile_block(const Seg& sg, const Tile& tl, int bi
         start = sg.csr[local];
         len = sg.csr[local + 1] - start;
     }
+}
+
+// Uniform blocks of whole 4-element vectors (nv = p / 4 <= 64 kHistVecs), taken by one wave
+// with kHistVecs vectors a lane in registers, all loaded before the first is used, so the
+// gradients are read once and each trip to memory brings kHistVecs vectors. J > 0: a block
+// takes J vectors of every lane, kHistVecs / J blocks at a time; J = 0: a block takes one
+// vector of each lane of a group of 2^lpb_log2 >= nv lanes, so a vector slot holds
+// 64 >> lpb_log2 blocks. Blocks [0, nblk) from element e0 of the tensor.
+//
+// The kernel is bound by the latency of its chain (loads, block maximum, bins): one block a
+// wave with two loads in flight and a second read for the bins took 405 us on the GPT-2
+// small shapes (124M float32 gradients in rows of 768) and 2.30 ms on the Llama-3 1.5B ones
+// (bfloat16, rows of 2048 and 8192); this takes 148 us and 1.22 ms. Not the flush: storing
+// each workgroup's bins and adding them up in a second kernel instead of the atomics left
+// both kernels' times as they were.
+constexpr int kHistVecs = 8;
+constexpr int64_t kHistVecGroups = 1024;   // four workgroups a CU
+
+// Elements e .. e + 3 (one vector when `aligned`).
+template <int GDT>
+__device__ __forceinline__ void hist_load(const void* grad, int64_t e, bool aligned, float g[4])
+{
+    if (!aligned) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            if (GDT == DT_F32)
+                g[c] = static_cast<const float*>(grad)[e + c];
+            else
+                g[c] = __uint_as_float(
+                    static_cast<uint32_t>(static_cast<const uint16_t*>(grad)[e + c]) << 16);
+        }
+    } else if (GDT == DT_F32) {
+        const f32x4 x = __builtin_nontemporal_load(
+            reinterpret_cast<const f32x4*>(static_cast<const float*>(grad) + e));
+        g[0] = x.x; g[1] = x.y; g[2] = x.z; g[3] = x.w;
+    } else {
+        const u32x2 x = __builtin_nontemporal_load(
+            reinterpret_cast<const u32x2*>(static_cast<const uint16_t*>(grad) + e));
+        g[0] = __uint_as_float(x.x << 16); g[1] = __uint_as_float(x.x & 0xffff0000u);
+        g[2] = __uint_as_float(x.y << 16); g[3] = __uint_as_float(x.y & 0xffff0000u);
+    }
+}
+
+__device__ __forceinline__ float max4(const float g[4])
+{
+    return fmaxf(fmaxf(fabsf(g[0]), fabsf(g[1])), fmaxf(fabsf(g[2]), fabsf(g[3])));
+}
+
+template <int GDT, int J>
+__device__ __forceinline__ void hist_blocks(const void* grad, bool aligned, int64_t e0, int nblk,
+                                            int nv, int lpb_log2, double half_nb, int nbins,
+                                            uint32_t* h, int lane)
+{
+    constexpr int V = kHistVecs;
+    constexpr int B = J ? V / J : 0;            // blocks at a time (J > 0)
+    const int per = J ? B : V * (64 >> lpb_log2);
+    const int sub = J ? 0 : lane >> lpb_log2;
+    const int li = J ? lane : lane & ((1 << lpb_log2) - 1);
+    for (int b0 = 0; b0 < nblk; b0 += per) {
+        float g[V][4];
+#pragma unroll
+        for (int u = 0; u < V; ++u) {
+            const int blk = J ? b0 + u / (J ? J : 1) : b0 + u * (64 >> lpb_log2) + sub;
+            const int v = J ? u % (J ? J : 1) * 64 + li : li;
+            g[u][0] = g[u][1] = g[u][2] = g[u][3] = 0.0f;
+            if (blk < nblk && v < nv && (!J || u < B * J)) {
+                hist_load<GDT>(grad, e0 + (static_cast<int64_t>(blk) * nv + v) * 4, aligned, g[u]);
+            }
+        }
+        constexpr int N = J ? B : V;   // maxima a lane takes part in
+        float a[N];
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            a[k] = 0.0f;
+#pragma unroll
+            for (int i = 0; i < (J ? J : 1); ++i) a[k] = fmaxf(a[k], max4(g[k * (J ? J : 1) + i]));
+        }
+        const int wl = J ? 64 : 1 << lpb_log2;
+        for (int off = 1; off < wl; off <<= 1)
+#pragma unroll
+            for (int k = 0; k < N; ++k) a[k] = fmaxf(a[k], __shfl_xor(a[k], off));
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            const HistBlock hb = hist_block(a[k]);
+            const int blk = J ? b0 + k : b0 + k * (64 >> lpb_log2) + sub;
+            if (!(a[k] > 0.0f) || blk >= nblk) continue;
+#pragma unroll
+            for (int i = 0; i < (J ? J : 1); ++i)
+                if ((J ? i * 64 + li : li) < nv)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        atomicAdd(&h[hist_bin(g[k * (J ? J : 1) + i][c], hb, half_nb, nbins)], 1u);
+        }
+    }
+}
+
+// Longer blocks: kHistVecs vectors a lane in flight, once for the maximum and once for the
+// bins (the last ones from registers).
+template <int GDT>
+__device__ __forceinline__ void hist_long(const void* grad, bool aligned, int64_t e0, int nblk,
+                                          int64_t nv, double half_nb, int nbins, uint32_t* h,
+                                          int lane)
+{
+    constexpr int V = kHistVecs;
+    for (int blk = 0; blk < nblk; ++blk) {
+        const int64_t b0 = e0 + 4 * nv * blk;
+        const int64_t last = (nv - 1) / (64 * V) * (64 * V);
+        float g[V][4];
+        float a = 0.0f;
+        for (int64_t v0 = 0; v0 <= last; v0 += 64 * V) {
+#pragma unroll
+            for (int u = 0; u < V; ++u) {
+                const int64_t v = v0 + u * 64 + lane;
+                g[u][0] = g[u][1] = g[u][2] = g[u][3] = 0.0f;
+                if (v < nv) hist_load<GDT>(grad, b0 + 4 * v, aligned, g[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < V; ++u) a = fmaxf(a, max4(g[u]));
+        }
+        for (int off = 1; off < 64; off <<= 1) a = fmaxf(a, __shfl_xor(a, off));
+        if (!(a > 0.0f)) continue;
+        const HistBlock hb = hist_block(a);
+        for (int64_t v0 = last; v0 >= 0; v0 -= 64 * V) {
+            if (v0 < last) {
+#pragma unroll
+                for (int u = 0; u < V; ++u)
+                    hist_load<GDT>(grad, b0 + 4 * (v0 + u * 64 + lane), aligned, g[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < V; ++u)
+                if (v0 + u * 64 + lane < nv)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        atomicAdd(&h[hist_bin(g[u][c], hb, half_nb, nbins)], 1u);
+        }
+    }
+}
+
+template <int GDT>
+__device__ __forceinline__ void hist_uniform(const Seg& sg, const Tile& tl, double half_nb,
+                                             int nbins, uint32_t* h, int lane)
+{
+    const uintptr_t al = GDT == DT_F32 ? 15 : 7;
+    const bool aligned = (reinterpret_cast<uintptr_t>(sg.grad) & al) == 0;
+    const int64_t nvec = sg.period >> 2;
+    const int n = tl.nblk;
+    if (nvec > 64 * kHistVecs) {
+        hist_long<GDT>(sg.grad, aligned, tl.elem0, n, nvec, half_nb, nbins, h, lane);
+        return;
+    }
+    const int nv = static_cast<int>(nvec);
+#define GEFEN_HIST(J, LL) \
+    hist_blocks<GDT, J>(sg.grad, aligned, tl.elem0, n, nv, LL, half_nb, nbins, h, lane)
+    if (nv <= 32) {
+        int ll = 0;
+        while ((1 << ll) < nv) ++ll;
+        GEFEN_HIST(0, ll);
+    } else if (nv <= 64) {
+        GEFEN_HIST(1, 6);
+    } else if (nv <= 128) {
+        GEFEN_HIST(2, 6);
+    } else if (nv <= 256) {
+        GEFEN_HIST(4, 6);
+    } else {
+        GEFEN_HIST(8, 6);
+    }
+#undef GEFEN_HIST
 }
 
 // Absolute maximum of |g| over one chunk of a huge block.
@@ -141,6 +304,9 @@ __global__ __launch_bounds__(kThreads) void k_hist_h_absmax(const Tile* __restri
     }
 }
 
+// VEC: the tiles of hist_by_vectors, else the others: a launch each, since the registers of
+// the first would halve the waves that hide the second's chains.
+template <bool VEC>
 __global__ __launch_bounds__(kThreads) void k_histogram(const Tile* __restrict__ tiles,
                                                         int64_t n_tiles,
                                                         const int32_t* __restrict__ tile_kind,
@@ -166,16 +332,24 @@ __global__ __launch_bounds__(kThreads) void k_histogram(const Tile* __restrict__
         const Tile tl = tiles[ti];
         const Seg sg = segs[tl.seg];
         const int kind = tile_kind[ti];
-        if (kind == KIND_L) {
+        if (hist_by_vectors(kind, sg.period) != VEC) continue;
+        if constexpr (VEC) {
+            if (sg.gdtype == DT_F32)
+                hist_uniform<DT_F32>(sg, tl, half_nb, nbins, h, lane);
+            else
+                hist_uniform<DT_BF16>(sg, tl, half_nb, nbins, h, lane);
+        } else if (kind == KIND_L) {
             // one lane per small block
             for (int bi = lane; bi < tl.nblk; bi += 64) {
                 int64_t start, len;
                 tile_block(sg, tl, bi, start, len);
                 float a = 0.0f;
                 for (int64_t i = 0; i < len; ++i) a = fmaxf(a, fabsf(grad_at(sg, start + i)));
-                if (a > 0.0f)
+                if (a > 0.0f) {
+                    const HistBlock hb = hist_block(a);
                     for (int64_t i = 0; i < len; ++i)
-                        atomicAdd(&h[bin_of(grad_at(sg, start + i), a, half_nb, nbins)], 1u);
+                        atomicAdd(&h[hist_bin(grad_at(sg, start + i), hb, half_nb, nbins)], 1u);
+                }
             }
         } else if (kind == KIND_H) {
             // one chunk of a huge block: block absmax from the chunk maxima
@@ -752,13 +926,19 @@ hipError_t launch_hist_h_absmax(const Tile* tiles, const HTile* htiles, int64_t 
 
 hipError_t launch_histogram(const Tile* tiles, int64_t n_tiles, const int32_t* tile_kind,
                             const HTile* htiles, const float* am_partials, const Seg* segs,
-                            int32_t nbins, uint64_t* hist, hipStream_t stream)
+                            int32_t nbins, uint64_t* hist, int32_t ways, hipStream_t stream)
 {
     if (n_tiles <= 0) return hipSuccess;
     const int64_t w = (n_tiles + kThreads / 64 - 1) / (kThreads / 64);
-    const int64_t g = w < 4096 ? w : 4096;
-    hipLaunchKernelGGL(k_histogram, dim3(static_cast<unsigned>(g)), dim3(kThreads), 0, stream,
-                       tiles, n_tiles, tile_kind, htiles, am_partials, segs, nbins, hist);
+    const auto grid = [&](int64_t most) {
+        return dim3(static_cast<unsigned>(w < most ? w : most));
+    };
+    if (ways & kHistVec)   // as many workgroups as are resident
+        hipLaunchKernelGGL(k_histogram<true>, grid(kHistVecGroups), dim3(kThreads), 0, stream,
+                           tiles, n_tiles, tile_kind, htiles, am_partials, segs, nbins, hist);
+    if (ways & kHistStream)
+        hipLaunchKernelGGL(k_histogram<false>, grid(4096), dim3(kThreads), 0, stream, tiles,
+                           n_tiles, tile_kind, htiles, am_partials, segs, nbins, hist);
     return hipGetLastError();
 }
 

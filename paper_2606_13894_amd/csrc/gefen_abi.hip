@@ -96,6 +96,7 @@ struct gefen_state {
     int64_t* csr = nullptr;
 
     uint64_t* hist = nullptr;
+    std::vector<int32_t> hist_ways;    // per class: the histogram kernels its tiles need
     void* dp_ws = nullptr;
     double* fit_cb64 = nullptr;
     double* fit_cost = nullptr;
@@ -306,6 +307,14 @@ int plan_tiles(gefen_state* st, const std::vector<std::vector<int64_t>>& starts)
     st->n_hblocks = ctx.n_hblocks;
     st->classes = plan.classes;
     st->n_tiles = static_cast<int64_t>(plan.tiles.size());
+    st->hist_ways.assign(plan.classes.size(), 0);
+    for (size_t ci = 0; ci < plan.classes.size(); ++ci)
+        for (int64_t i = 0; i < plan.classes[ci].count; ++i) {
+            const size_t at = static_cast<size_t>(plan.classes[ci].first + i);
+            st->hist_ways[ci] |=
+                hist_by_vectors(plan.kinds[at], st->explicit_blocks ? 0 : st->period[plan.tiles[at].seg])
+                    ? kHistVec : kHistStream;
+        }
     int rc = st->alloc(&st->tiles, sizeof(Tile) * plan.tiles.size(), false);
     if (rc) return rc;
     rc = st->alloc(&st->tile_kind, sizeof(int32_t) * plan.kinds.size(), false);
@@ -431,12 +440,14 @@ CodebookDev codebook_dev(const gefen_state* st)
 // Histogram with the state's blocks into `hist` (already zeroed).
 int run_histogram(gefen_state* st, uint64_t* hist, hipStream_t stream)
 {
+    int32_t ways = 0;
+    for (int32_t w : st->hist_ways) ways |= w;
     for (const Class& c : st->classes)
         if (c.kind == KIND_H)
             GEFEN_HIP(launch_hist_h_absmax(st->tiles + c.first, st->htiles + c.first, c.count,
                                            st->segs, st->h_absmax, stream));
     GEFEN_HIP(launch_histogram(st->tiles, st->n_tiles, st->tile_kind, st->htiles, st->h_absmax,
-                               st->segs, st->nbins, hist, stream));
+                               st->segs, st->nbins, hist, ways, stream));
     return GEFEN_OK;
 }
 
@@ -749,7 +760,7 @@ int step_impl(gefen_state* st, const gefen_tensor* params, const gefen_tensor* g
                                                st->h_absmax, stream));
             GEFEN_HIP(launch_histogram(tiles, c.count, st->tile_kind + c.first,
                                        st->htiles + c.first, st->h_absmax, st->segs, st->nbins,
-                                       st->hist, stream));
+                                       st->hist, st->hist_ways[ci], stream));
         }
     }
     if (prof) ++st->prof_steps;

@@ -56,10 +56,43 @@ struct CodebookDev {
 // histogram kernel and the step kernels that take the histogram on the way bin every
 // element identically. (A float32 estimate with a float64 evaluation near bin edges
 // measured slower in both kernels: a wave almost always holds some lane near an edge.)
-__device__ __forceinline__ int hist_bin(float g, float a, double half_nb, int nbins)
+//
+// The quotient is the correctly rounded g / a without a division per element: with inv =
+// RN(1 / a) once per block, q = RN(g inv) is within 2 ulp, r = g - q a is exact (a multiple
+// of ulp(q) times the last place of a, at most 2^25 of them: a has 24 bits), and q + r inv
+// is off by less than 2^-51 ulp before its one rounding. The quotient of two 24-bit numbers
+// lies on no rounding boundary of float64 and no nearer to one than 2^-25 ulp, so that
+// rounding is g / a's. float32 values leave the exponents far from float64's limits. An
+// infinite a takes zeros instead: finite g gives x = 0, infinite g a NaN, as g / a does.
+// (Three multiply-adds against about a dozen dependent operations of the division.)
+// Tiles whose blocks the histogram kernel takes by 4-element vectors from the block's first
+// element on: uniform blocks of whole vectors that one workgroup's tile holds whole.
+__host__ __device__ __forceinline__ bool hist_by_vectors(int32_t kind, int64_t period)
 {
-    const double x = static_cast<double>(g) / static_cast<double>(a);
-    const int b = static_cast<int>((x + 1.0) * half_nb);
+    return kind != KIND_H && period > 0 && period % 4 == 0;
+}
+
+struct HistBlock {
+    double a, inv;
+};
+
+__host__ __device__ __forceinline__ HistBlock hist_block(float a)
+{
+    if (a > 3.4028234663852886e38f) return {0.0, 0.0};
+    const double d = static_cast<double>(a);
+    return {d, 1.0 / d};
+}
+
+__host__ __device__ __forceinline__ double hist_quotient(float g, const HistBlock& b)
+{
+    const double d = static_cast<double>(g);
+    const double q = d * b.inv;
+    return fma(fma(-q, b.a, d), b.inv, q);
+}
+
+__device__ __forceinline__ int hist_bin(float g, const HistBlock& blk, double half_nb, int nbins)
+{
+    const int b = static_cast<int>((hist_quotient(g, blk) + 1.0) * half_nb);
     return b < nbins - 1 ? b : nbins - 1;
 }
 
@@ -90,9 +123,11 @@ hipError_t launch_step_g_hist(int gdtype, int code_bits, const Tile* tiles, int6
 // launch_hist_h_absmax over each KIND_H class range writes am_partials[first + chunk].
 hipError_t launch_hist_h_absmax(const Tile* tiles, const HTile* htiles, int64_t n_tiles,
                                 const Seg* segs, float* am_partials, hipStream_t stream);
+// `ways` says which of the two kernels have tiles in the range (hist_by_vectors).
+enum : int32_t { kHistVec = 1, kHistStream = 2 };
 hipError_t launch_histogram(const Tile* tiles, int64_t n_tiles, const int32_t* tile_kind,
                             const HTile* htiles, const float* am_partials, const Seg* segs,
-                            int32_t nbins, uint64_t* hist, hipStream_t stream);
+                            int32_t nbins, uint64_t* hist, int32_t ways, hipStream_t stream);
 
 // DP over a device histogram. ws must hold dp_workspace_bytes(nbins, k) bytes.
 size_t dp_workspace_bytes(int32_t nbins, int32_t k);

@@ -468,6 +468,8 @@ __device__ __forceinline__ void pass_update(const LdsTables& L, const Seg& sg,
     const int tid = threadIdx.x;
     float* __restrict__ th = sg.theta;
     const int64_t cj = sg.code_off;
+    HistBlock hb = {0.0, 0.0};
+    if constexpr (HG) hb = hist_block(ag);
     for (int64_t v0 = sp.vb + tid; v0 < sp.ve; v0 += static_cast<int64_t>(BS) * UNR) {
         float g[UNR][4];
         uint32_t q4[UNR];
@@ -495,7 +497,7 @@ __device__ __forceinline__ void pass_update(const LdsTables& L, const Seg& sg,
                     packed |= static_cast<uint32_t>(q) << (CB * c);
                     out[c] = fmaf(-bo.r, mm, tv[c] * sc.decay);
                     if constexpr (HG)
-                        if (ag > 0.0f) atomicAdd(&hl[hist_bin(g[u][c], ag, half_nb, nbins)], 1u);
+                        if (ag > 0.0f) atomicAdd(&hl[hist_bin(g[u][c], hb, half_nb, nbins)], 1u);
                 }
                 const f32x4 o4 = {out[0], out[1], out[2], out[3]};
                 __builtin_nontemporal_store(o4, glw<f32x4>(th) + v);
@@ -512,7 +514,7 @@ __device__ __forceinline__ void pass_update(const LdsTables& L, const Seg& sg,
         th[e] = fmaf(-bo.r, mm, th[e] * sc.decay);
         code_st<CB>(codes, cj + e, q0, q);
         if constexpr (HG)
-            if (ag > 0.0f) atomicAdd(&hl[hist_bin(g, ag, half_nb, nbins)], 1u);
+            if (ag > 0.0f) atomicAdd(&hl[hist_bin(g, hb, half_nb, nbins)], 1u);
     }
 }
 
@@ -558,6 +560,7 @@ struct RunLdsT {
     float s_old[kRunMaxBlocks], v_old[kRunMaxBlocks];
     float s_new[kRunMaxBlocks], r[kRunMaxBlocks], inv_s[kRunMaxBlocks];
     float ag[HG ? kRunMaxBlocks : 1];
+    HistBlock hb[HG ? kRunMaxBlocks : 1];
     float part[kRunMaxVec][HG ? 6 : 4];
 };
 
@@ -685,7 +688,10 @@ __device__ __forceinline__ void run_tile(LdsTables& L, RunLdsT<HG>& R, const Til
             if constexpr (HG) ag = fmaxf(ag, __shfl_xor(ag, off));
         }
         if (lane == 0) {
-            if constexpr (HG) R.ag[k] = ag;
+            if constexpr (HG) {
+                R.ag[k] = ag;
+                R.hb[k] = hist_block(ag);
+            }
             const BlockOut bo = finish_block(ss, am, R.v_old[k], static_cast<float>(be - bs), sc);
             scale[tl.blk0 + k] = bo.s_new;
             vmom[tl.blk0 + k] = bo.v_new;
@@ -718,7 +724,7 @@ __device__ __forceinline__ void run_tile(LdsTables& L, RunLdsT<HG>& R, const Til
             if constexpr (HG) {
                 const int64_t x = e + c;
                 if (x >= e_lo && x < e_hi && R.ag[k] > 0.0f)
-                    atomicAdd(&hl[hist_bin(gk[j][c], R.ag[k], half_nb, nbins)], 1u);
+                    atomicAdd(&hl[hist_bin(gk[j][c], R.hb[k], half_nb, nbins)], 1u);
             }
         }
         if (aligned && e >= e_lo && e + 4 <= e_hi) {
