@@ -182,7 +182,7 @@ int gefen_dp_codebook(const uint64_t* hist, int32_t nbins, int32_t k, double* co
 /* gefen_dp_codebook_static -- gefen_dp_codebook for callers that cannot allocate device
  * memory (code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc): the same DP, the same kernels and the same results, with its workspace in
- * one fixed array per GPU that the library holds until the process ends (3 MiB; enough
+ * one fixed array per GPU that the library holds until the process ends (11 MiB; enough
  * for the largest DP, 4096 bins and 256 entries). It calls no hipMalloc, hipFree or other
  * allocating routine. Arguments, outputs and errors as gefen_dp_codebook; a DP larger
  * than the fixed workspace is refused with EINVAL. The first call on a device looks up

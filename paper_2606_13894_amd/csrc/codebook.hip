@@ -383,21 +383,25 @@ __global__ __launch_bounds__(kThreads) void k_histogram(const Tile* __restrict__
 // The DP (Alg. 3, App. D): D[j][r] = min over l of D[j-1][l-1] + C(l, r), argmin to the
 // smallest l, over the b non-empty bins. Workspace (all 256-byte aligned):
 //   hdr    int32[16]: [0] b (non-empty bins), [1] keff (entries the DP solves for),
-//          [2] status, [3] 1 when rows may be pruned (dp_may_prune)
+//          [2] status, [3] 1 when rows may be pruned (dp_may_prune), [4] row tiles handed
+//          out by k_dp_run, [5] 1 when one of its waits ran out
 //   Z0,Z1,Z2,cnt,ctr   double[NB + 1] each (1-based, index 0 = 0)
-//   D      double[2][NB + 1]   D[j][r], by the parity of j
-//   from   uint16[2][NB + 1]   smallest l that a row of level j + 1 needs to look at
-//   anc    uint16[2][NB + 1]   row of the path at the last checkpoint level before j
+//   D      double[k][NB + 1]   D[j][r]; from level kDpEntry on kDpUnset until written
+//   from   uint16[2][NB + 1]   smallest l that a row of level j + 1 needs to look at, by
+//          the parity of j (levels before kDpEntry)
 //   split  uint16[k + 1][NB + 1]   the argmin l
-//   jump   uint16[k / kDpCheck + 1][NB + 1]   anc at the checkpoint levels
+//   jump   uint16[k / kDpCheck + 1][NB + 1]   k_dp_jump
 // ---------------------------------------------------------------------------------
 struct DpLayout {
-    size_t hdr, z0, z1, z2, cnt, ctr, d, from, anc, split, jump, total;
+    size_t hdr, z0, z1, z2, cnt, ctr, d, from, split, jump, total;
 };
 
 constexpr int kDpThreads = 256;
 constexpr int kDpRows = kDpThreads / 64;   // rows r per workgroup, one wave each
 constexpr int kDpCheck = 16;               // levels between checkpoints of the backtrack
+constexpr int kDpEntry = 8;                // levels before it take a launch each
+constexpr int kDpFill = 64;                // workgroups that mark D unset
+constexpr unsigned long long kDpUnset = ~0ULL;   // a NaN; D holds none
 
 __host__ __device__ inline size_t align256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
 
@@ -412,9 +416,8 @@ __host__ __device__ inline DpLayout dp_layout(int32_t nbins, int32_t k)
     L.z2 = o; o += align256(row * sizeof(double));
     L.cnt = o; o += align256(row * sizeof(double));
     L.ctr = o; o += align256(row * sizeof(double));
-    L.d = o; o += align256(2 * row * sizeof(double));
+    L.d = o; o += align256(static_cast<size_t>(k) * row * sizeof(double));
     L.from = o; o += align256(2 * row * sizeof(uint16_t));
-    L.anc = o; o += align256(2 * row * sizeof(uint16_t));
     L.split = o; o += align256(static_cast<size_t>(k + 1) * row * sizeof(uint16_t));
     L.jump = o; o += align256(static_cast<size_t>(k / kDpCheck + 1) * row * sizeof(uint16_t));
     L.total = o;
@@ -476,6 +479,14 @@ __global__ __launch_bounds__(kThreads) void k_dp_prep(const uint64_t* __restrict
     __shared__ int nr;
     const int tid = threadIdx.x;
     const DpLayout L = dp_layout(nbins, k);
+    if (blockIdx.x > 0) {   // beside the chain of workgroup 0: the levels of k_dp_run unset
+        const int64_t row = nbins + 1;
+        unsigned long long* d = at<unsigned long long>(ws, L.d);
+        for (int64_t i = kDpEntry * row + (blockIdx.x - 1) * kThreads + tid; i < k * row;
+             i += static_cast<int64_t>(gridDim.x - 1) * kThreads)
+            d[i] = kDpUnset;
+        return;
+    }
     double* cnt = at<double>(ws, L.cnt);
     double* ctr = at<double>(ws, L.ctr);
     const double w = 2.0 / static_cast<double>(nbins);
@@ -556,6 +567,7 @@ __global__ __launch_bounds__(kThreads) void k_dp_prep(const uint64_t* __restrict
         hdr[1] = b >= k ? k : (b >= 2 ? b : 0);
         hdr[2] = b >= k ? 0 : 1;
         hdr[3] = dp_may_prune(t[0][b], nbins) ? 1 : 0;
+        hdr[4] = hdr[5] = 0;
     }
     double* Z0 = at<double>(ws, L.z0);
     double* Z1 = at<double>(ws, L.z1);
@@ -563,7 +575,6 @@ __global__ __launch_bounds__(kThreads) void k_dp_prep(const uint64_t* __restrict
     const size_t row = static_cast<size_t>(nbins) + 1;
     double* D1 = at<double>(ws, L.d) + row;
     uint16_t* from1 = at<uint16_t>(ws, L.from) + row;
-    uint16_t* anc1 = at<uint16_t>(ws, L.anc) + row;
     uint16_t* split1 = at<uint16_t>(ws, L.split) + row;
     for (int q = tid; q <= b; q += kThreads) {
         const double z0 = t[0][q], z1 = t[1][q], z2 = t[2][q];
@@ -572,7 +583,6 @@ __global__ __launch_bounds__(kThreads) void k_dp_prep(const uint64_t* __restrict
         Z2[q] = z2;
         D1[q] = q == 0 ? INFINITY : 0.0 + dp_cost_forced(-1.0, z0, z1, z2, 0.0, 0.0, 0.0);
         from1[q] = 1;
-        anc1[q] = 0;
         split1[q] = 1;
     }
 }
@@ -603,7 +613,7 @@ __device__ __forceinline__ double wave_min(double v)
 }
 
 // ---------------------------------------------------------------------------------
-// DP level j, 2 <= j < keff: a wave takes one row r and its candidates l, 64 at a time
+// DP level j, 2 <= j < keff and j < kDpEntry: a wave takes one row r and its candidates l, 64 at a time
 // from l = r down to the row's lower bound. Only the rows r <= b - (keff - j) are taken: a
 // longer prefix leaves too few bins for the entries still to come, so no path to
 // D[keff][b] passes through it.
@@ -638,13 +648,12 @@ __global__ __launch_bounds__(kDpThreads) void k_dp_level(int32_t nbins, int32_t 
 {
     const DpLayout L = dp_layout(nbins, k);
     const size_t row = static_cast<size_t>(nbins) + 1;
-    const size_t cur = (j & 1) * row, prev = row - cur;
+    const size_t cur = (j & 1) * row, prev = row - cur;   // of `from`
     const double* __restrict__ Z0 = at<double>(ws, L.z0);
     const double* __restrict__ Z1 = at<double>(ws, L.z1);
     const double* __restrict__ Z2 = at<double>(ws, L.z2);
-    const double* __restrict__ Dp = at<double>(ws, L.d) + prev;
+    const double* __restrict__ Dp = at<double>(ws, L.d) + (j - 1) * row;
     const uint16_t* __restrict__ fp = at<uint16_t>(ws, L.from) + prev;
-    const uint16_t* __restrict__ ap = at<uint16_t>(ws, L.anc) + prev;
     const int32_t* __restrict__ hdr = at<int32_t>(ws, L.hdr);
     const int lane = threadIdx.x & 63;
     const int r = j + static_cast<int>(blockIdx.x) * kDpRows +
@@ -653,7 +662,6 @@ __global__ __launch_bounds__(kDpThreads) void k_dp_level(int32_t nbins, int32_t 
     // l - 1 of this lane's first candidate, kept inside the arrays
     const int x0 = r - 1 - lane > 0 ? r - 1 - lane : 0;
     double z0 = Z0[x0], z1 = Z1[x0], z2 = Z2[x0], dv = Dp[x0];
-    int av = ap[x0];
     const double zr0 = Z0[r], zr1 = Z1[r], zr2 = Z2[r];
     const int f0 = fp[r], f1 = fp[r - 1];
     const int b = hdr[0], keff = hdr[1], prune = hdr[3];
@@ -665,14 +673,13 @@ __global__ __launch_bounds__(kDpThreads) void k_dp_level(int32_t nbins, int32_t 
         lo = f > j ? f : j;
     }
     double best = INFINITY;
-    int arg = 0, anc = 0;
+    int arg = 0;
     double first = INFINITY;   // the first chunk's candidate
     if (r - lane >= lo) {
         const double c = dv + dp_cost_free(zr0, zr1, zr2, z0, z1, z2);
         if (c < INFINITY) {   // counts past 2^53 can make an empty interval: NaN
             first = best = c;
             arg = r - lane;
-            anc = av;
         }
     }
     for (int l = r - 64 - lane; l >= lo; l -= 64) {   // falling l: the last minimum kept
@@ -680,7 +687,6 @@ __global__ __launch_bounds__(kDpThreads) void k_dp_level(int32_t nbins, int32_t 
         if (c <= best && c < INFINITY) {
             best = c;
             arg = l;
-            anc = ap[l - 1];
         }
     }
     const double m = wave_min(best);
@@ -718,21 +724,370 @@ __global__ __launch_bounds__(kDpThreads) void k_dp_level(int32_t nbins, int32_t 
             if (base + 63 >= bestl) break;
         }
     }
-    const int w = (r - bestl) & 63;   // the lane that has it
-    const int up = (j - 1) % kDpCheck == 0 ? bestl - 1 : __builtin_amdgcn_readlane(anc, w);
     if (lane == 0) {
-        at<double>(ws, L.d)[cur + r] = m;
+        at<double>(ws, L.d)[j * row + r] = m;
         at<uint16_t>(ws, L.from)[cur + r] = static_cast<uint16_t>(from);
-        at<uint16_t>(ws, L.anc)[cur + r] = static_cast<uint16_t>(up);
-        at<uint16_t>(ws, L.split)[static_cast<size_t>(j) * row + r] = static_cast<uint16_t>(bestl);
-        if (j % kDpCheck == 0)
-            at<uint16_t>(ws, L.jump)[static_cast<size_t>(j / kDpCheck) * row + r] =
-                static_cast<uint16_t>(up);
+        at<uint16_t>(ws, L.split)[j * row + r] = static_cast<uint16_t>(bestl);
     }
 }
 
+// ---------------------------------------------------------------------------------
+// DP levels kDpEntry <= j < keff in one launch. A workgroup owns kDpTile consecutive rows at
+// every level, in LDS: the prefix sums, D of the level before for its rows and, below them,
+// for the rows its candidates reach. Its own rows stay there; the others' come from global
+// memory, where every D is written once and is kDpUnset before, so that a value is its own
+// flag: a reader loads it ahead (while it computes the level before) and polls it only where
+// it was not there yet. D goes through agent-scope atomics, since the tiles run on all XCDs.
+//
+// Progress. A tile reads only lower tiles' rows, and tiles are handed out in the order in
+// which the workgroups start, so whoever a workgroup waits for has started and itself waits
+// for nothing higher: no assumption on residency or dispatch order is needed. Waits are
+// bounded all the same (kDpSpin polls, seconds); one that runs out ends its workgroup, and
+// k_dp_last reports it as status 2 with the uniform codebook.
+//
+// Lower bounds, candidates, slack and tie rules are k_dp_level's. A lane takes a row and one
+// of its candidates, kDpChunk of them from the row's lower bound up, into `cand`; after a
+// barrier sixteen lanes a row form its minimum and argmins. (A wave a row, as in k_dp_level,
+// needs about six times the instructions where windows hold few candidates, which one CU
+// cannot hide.)
+//
+// Upper bound. Windows [from, r] are as long as the intervals: hundreds of bins at the first
+// levels and in thinly filled stretches. No row below R needs a candidate above the largest l
+// that lies within slack of R's minimum: by (a), read downwards, l stays worse than R's
+// argmin by as much at r < R, and the rounding at r is no larger than at R (Z0[r] <= Z0[R],
+// and R's argmin costs less at r). So where a tile has a window of more than kDpChunk, half
+// of the waves scan the window of its highest row while the other half take the rows' first
+// kDpChunk / 2 candidates; mostly the scan then shows these to be all that is needed (the
+// tile's rows plus the shift of the argmin between two levels), else the bound is found and
+// the windows taken chunk by chunk, once for the minimum and once for `from`. (Without it
+// level 8 alone took 52 us.)
+//
+// A launch and two trips to memory made every level 4.1-6.5 us, 1.1 ms from level 8 to 255
+// at 4096 bins; this takes 0.55 ms, 1.9-2.4 us a level in every tile: the latency of the two
+// barriers, the interval cost's float64 division and the sixteen lanes' minimum. Waves
+// without candidates that skip their part leave it at that, tiles of 32 rows (two candidates
+// a lane) take 0.75-0.95 ms. The whole DP: 1.37 -> 0.77 ms (4096 bins, 256 entries). Before
+// kDpEntry the windows are so long that all CUs on one level are faster (8-30 us).
+// ---------------------------------------------------------------------------------
+constexpr int kDpTile = 16;
+constexpr int kDpRunThreads = 1024;
+constexpr int kDpHalf = kDpRunThreads / 2;
+constexpr int kDpWaves = kDpRunThreads / 64;
+constexpr int kDpChunk = kDpRunThreads / kDpTile;   // candidates of a row at once
+constexpr int kDpEach = kDpChunk / 16;              // of one lane in the minimum
+constexpr int kDpPitch = kDpTile + 1;   // doubles; a row's candidates hit distinct banks
+constexpr int kDpSpin = 1 << 20;
+
+// Workgroup barrier for LDS only: global loads and stores stay in flight.
+__device__ __forceinline__ void lds_barrier()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+__device__ __forceinline__ unsigned long long dp_load(const unsigned long long* p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Smallest of a row of sixteen lanes' doubles (no NaN), in each of them; the same for ints.
+__device__ __forceinline__ double row_min(double v)
+{
+    v = dpp_min<0xB1>(v);
+    v = dpp_min<0x4E>(v);
+    v = dpp_min<0x141>(v);
+    return dpp_min<0x140>(v);
+}
+
+template <int CTRL>
+__device__ __forceinline__ int dpp_imin(int v)
+{
+    const int o = __builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, 0xf, false);
+    return o < v ? o : v;
+}
+
+__device__ __forceinline__ int row_imin(int v)
+{
+    v = dpp_imin<0xB1>(v);
+    v = dpp_imin<0x4E>(v);
+    v = dpp_imin<0x141>(v);
+    return dpp_imin<0x140>(v);
+}
+
+__global__ __launch_bounds__(kDpRunThreads) void k_dp_run(int32_t nbins, int32_t k, void* ws)
+{
+    __shared__ double zs[3][kMaxBins + 1];
+    __shared__ double ds[kMaxBins + 1];
+    __shared__ double cand[kDpChunk * kDpPitch];
+    __shared__ double wmin[8], whigh[8];   // the scan's minima, by wave: all, and above the chunk
+    __shared__ int lo[kDpTile];
+    // by level parity: largest window and smallest lower bound of the level's rows, smallest
+    // lower bound of all rows still to come
+    __shared__ int wide[2], low[2], reach[2];
+    __shared__ int first_in, last_in;   // largest and smallest l within slack, as rt - l
+    __shared__ int tile_s, dead;
+    const DpLayout L = dp_layout(nbins, k);
+    const int64_t row = nbins + 1;
+    int32_t* hdr = at<int32_t>(ws, L.hdr);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (tid == 0) {   // the tile in order of the workgroups' starts
+        tile_s = atomicAdd(&hdr[4], 1);
+        dead = 0;
+        wide[0] = wide[1] = 0;
+        low[0] = low[1] = reach[0] = reach[1] = first_in = 0x7fffffff;
+        last_in = -1;
+    }
+    __syncthreads();
+    const int b = hdr[0], keff = hdr[1];
+    const bool prune = hdr[3] != 0;
+    const int R0 = 1 + tile_s * kDpTile;
+    // rows [j, b - keff + j] at level j: the first level with a row of this tile
+    const int lift = b - keff;
+    const int j0 = R0 - lift > kDpEntry ? R0 - lift : kDpEntry;
+    if (j0 >= keff || R0 + kDpTile - 1 < j0) return;
+    unsigned long long* D = at<unsigned long long>(ws, L.d);
+    uint16_t* split = at<uint16_t>(ws, L.split);
+    {
+        // lower bounds from the last level of its own launch; rows it did not have take
+        // those of its last row (they hold for all higher rows and levels)
+        const int rm = lift + kDpEntry - 1;
+        const uint16_t* from = at<uint16_t>(ws, L.from) + ((kDpEntry - 1) & 1) * row;
+        if (tid < kDpTile) {
+            const int r = R0 + tid;
+            const int f = prune && r >= kDpEntry ? from[r < rm ? r : rm] : 0;
+            const int v = f > j0 ? f : j0;
+            lo[tid] = v;
+            if (r >= j0) {
+                atomicMin(&reach[j0 & 1], v);
+                if (r <= lift + j0) {
+                    atomicMin(&low[j0 & 1], v);
+                    atomicMax(&wide[j0 & 1], r - v + 1);
+                }
+            }
+        }
+        __syncthreads();
+    }
+    int lmin = reach[j0 & 1];
+    const int top = R0 + kDpTile - 1 < b ? R0 + kDpTile - 1 : b;
+    for (int x = lmin - 1 + tid; x <= top; x += kDpRunThreads) {
+        zs[0][x] = at<double>(ws, L.z0)[x];
+        zs[1][x] = at<double>(ws, L.z1)[x];
+        zs[2][x] = at<double>(ws, L.z2)[x];
+        if (j0 == kDpEntry && x >= R0)
+            ds[x] = at<double>(ws, L.d)[(kDpEntry - 1) * row + x];
+    }
+    const int q = tid % kDpTile, slot = tid / kDpTile;   // candidates: this lane's row
+    const int cq = tid >> 4, sub = tid & 15;             // minima: this lane's row
+    const bool minima = tid < 16 * kDpTile;
+    unsigned long long ahead = kDpUnset;
+    for (int j = j0; j < keff; ++j) {
+        const int rmax = lift + j;
+        if (top < j) break;
+        {   // D[j-1] of the rows below the tile
+            const int x0 = (lmin > j ? lmin : j) - 1;
+            const unsigned long long* Dp = D + (j - 1) * row;
+            unsigned long long v = ahead;
+            for (int x = R0 - 1 - tid; x >= x0; x -= kDpRunThreads) {
+                for (int spin = 0; v == kDpUnset; ++spin) {
+                    v = dp_load(Dp + x);
+                    if (v != kDpUnset) break;
+                    if (spin == kDpSpin) {
+                        dead = 1;
+                        break;
+                    }
+                    __builtin_amdgcn_s_sleep(1);
+                }
+                ds[x] = __builtin_bit_cast(double, v);
+                v = kDpUnset;
+            }
+            const int x = R0 - 1 - tid;
+            ahead = kDpUnset;
+            if (x >= x0 && x >= j) ahead = dp_load(Dp + row + x);
+        }
+        lds_barrier();
+        if (dead) {
+            if (tid == 0) atomicExch(&hdr[5], 1);
+            return;
+        }
+        int W = wide[j & 1];
+        const int llow = low[j & 1];
+        lmin = reach[j & 1];
+        if (tid == 0) {
+            wide[(j + 1) & 1] = 0;
+            low[(j + 1) & 1] = reach[(j + 1) & 1] = 0x7fffffff;
+        }
+        const int r = R0 + q, cr = R0 + cq;
+        int lq = r >= j && r <= rmax ? lo[q] : 0x7fffffff;
+        int lc = minima ? lo[cq] : 0;
+        int hi = 0x7fffffff;   // no row needs a candidate above
+        const double zr0 = zs[0][r], zr1 = zs[1][r], zr2 = zs[2][r];
+        const double slack1 = 1.1102230246251565e-16 * 32.0 * static_cast<double>(k);
+        const double slack0 = minima ? 1.1102230246251565e-16 * 256.0 * zs[0][cr] : 0.0;
+        auto candidates = [&](int c0) {
+            const int l = lq + c0 + slot;
+            double c = INFINITY;
+            if (lq < 0x7fffffff && l <= r && l <= hi) {
+                const double f = ds[l - 1] + dp_cost_free(zr0, zr1, zr2, zs[0][l - 1], zs[1][l - 1],
+                                                          zs[2][l - 1]);
+                if (f < INFINITY) c = f;
+            }
+            cand[slot * kDpPitch + q] = c;
+        };
+        double m = INFINITY, near = INFINITY;
+        int ib = 0x7fffffff, in = 0x7fffffff;   // l = lc + index
+        // the first `each` x 16 candidates of `cand`, starting at c0: minimum, argmins
+        auto reduce = [&](int c0, int each, bool value, bool argnear) {
+            double v[kDpEach];
+#pragma unroll
+            for (int u = 0; u < kDpEach; ++u)
+                v[u] = u < each ? cand[(u * 16 + sub) * kDpPitch + cq] : INFINITY;
+            if (value) {
+                double n = v[0];
+#pragma unroll
+                for (int u = 1; u < kDpEach; ++u) n = fmin(n, v[u]);
+                n = row_min(n);
+                int f = 0x7fffffff;
+#pragma unroll
+                for (int u = kDpEach - 1; u >= 0; --u)
+                    if (v[u] == n) f = c0 + u * 16 + sub;
+                f = row_imin(f);
+                if (n < m) {   // rising l: the first minimum kept
+                    m = n;
+                    ib = f;
+                }
+                near = m + (slack0 + slack1 * m);
+            }
+            if (argnear) {
+                int f = 0x7fffffff;
+#pragma unroll
+                for (int u = kDpEach - 1; u >= 0; --u)
+                    if (v[u] <= near) f = c0 + u * 16 + sub;
+                f = row_imin(f);
+                in = f < in ? f : in;
+            }
+        };
+        bool done = false;
+        if (prune && W > kDpChunk) {
+            const int rt = top < rmax ? top : rmax, lt = lo[rt - R0];
+            const int g = llow + kDpChunk / 2 - 1;
+            const double t0 = zs[0][rt], t1 = zs[1][rt], t2 = zs[2][rt];
+            auto cost = [&](int l) {
+                const double c = ds[l - 1] + dp_cost_free(t0, t1, t2, zs[0][l - 1], zs[1][l - 1],
+                                                          zs[2][l - 1]);
+                return c < INFINITY ? c : INFINITY;
+            };
+            if (tid < kDpHalf) {
+                candidates(0);
+            } else {
+                double a = INFINITY, h = INFINITY;
+                for (int l = rt - (tid - kDpHalf); l >= lt; l -= kDpHalf) {
+                    const double c = cost(l);
+                    a = fmin(a, c);
+                    if (l > g) h = fmin(h, c);
+                }
+                a = wave_min(a);
+                h = wave_min(h);
+                if (lane == 0) {
+                    wmin[wave - 8] = a;
+                    whigh[wave - 8] = h;
+                }
+            }
+            lds_barrier();
+            const double mt = row_min(wmin[lane & 7]);
+            const double mh = row_min(whigh[lane & 7]);
+            const double neart = mt + (1.1102230246251565e-16 * 256.0 * t0 + slack1 * mt);
+            if (mh > neart) {
+                if (minima) reduce(0, kDpEach / 2, true, true);
+                done = true;
+            } else if (mt < INFINITY) {
+                int fi = 0x7fffffff, la = -1;
+                for (int x = wave * 64; rt - x >= lt; x += kDpRunThreads) {
+                    const int l = rt - x - lane;
+                    const unsigned long long hit = __ballot(l >= lt && cost(l >= lt ? l : lt) <= neart);
+                    if (hit) {
+                        const int f = x + __builtin_ctzll(hit);
+                        fi = f < fi ? f : fi;
+                        la = x + 63 - __builtin_clzll(hit);
+                    }
+                }
+                if (lane == 0 && la >= 0) {
+                    atomicMin(&first_in, fi);
+                    atomicMax(&last_in, la);
+                }
+                lds_barrier();
+                hi = rt - first_in;
+                int from = llow;
+                if (rt == R0 || rt == j) {   // the level's only row here
+                    from = rt - last_in;
+                    if (r == rt) lq = from;
+                    if (cr == rt) lc = from;
+                }
+                W = W < hi - from + 1 ? W : hi - from + 1;
+                lds_barrier();   // `cand` is rewritten, the two bounds are reset
+                if (tid == 0) {
+                    first_in = 0x7fffffff;
+                    last_in = -1;
+                }
+            }
+        }
+        for (int pass = 0; pass < 2 && !done; ++pass) {
+            done = W <= kDpChunk;
+            for (int c0 = 0; c0 < W; c0 += kDpChunk) {
+                if (pass > 0 || c0 > 0) lds_barrier();   // the chunk before is read
+                candidates(c0);
+                lds_barrier();
+                if (minima) reduce(c0, kDpEach, pass == 0, pass > 0 || done);
+            }
+        }
+        if (minima && sub == 0 && cr >= j && cr <= rmax) {
+            const int bestl = m < INFINITY ? lc + ib : lc;
+            const int from = m < INFINITY ? lc + in : lc;
+            ds[cr] = m;
+            __hip_atomic_store(D + j * row + cr, __builtin_bit_cast(unsigned long long, m),
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            split[j * row + cr] = static_cast<uint16_t>(bestl);
+            const int p = (j + 1) & 1;
+            int v = prune && from > j + 1 ? from : j + 1;
+            lo[cq] = v;
+            if (cr > j) {
+                atomicMax(&wide[p], cr - v + 1);
+                atomicMin(&low[p], v);
+                atomicMin(&reach[p], v);
+            }
+            if (cr == rmax && cq + 1 < kDpTile) {   // the row that level j + 1 adds
+                const int o = lo[cq + 1];
+                v = v > o ? v : o;
+                lo[cq + 1] = v;
+                atomicMax(&wide[p], cr + 1 - v + 1);
+                atomicMin(&low[p], v);
+                atomicMin(&reach[p], o);   // those after it still have their first bound
+            }
+        }
+    }
+}
+
+// jump[s][x], s >= 1: the path's row at level s kDpCheck from row x at the upper end of that
+// stretch, level (s + 1) kDpCheck or keff - 1. A thread each, at most kDpCheck dependent
+// reads.
+__global__ __launch_bounds__(256) void k_dp_jump(int32_t nbins, int32_t k, void* ws)
+{
+    const DpLayout L = dp_layout(nbins, k);
+    const int64_t row = nbins + 1;
+    const int32_t* hdr = at<int32_t>(ws, L.hdr);
+    const int b = hdr[0], keff = hdr[1];
+    const int base = (blockIdx.y + 1) * kDpCheck;
+    if (base > keff - 2 || hdr[5]) return;
+    const int top = base + kDpCheck < keff - 1 ? base + kDpCheck : keff - 1;
+    int x = blockIdx.x * 256 + threadIdx.x;
+    if (x < top || x > b - keff + top) return;   // rows of level `top`
+    const int x0 = x;
+    const uint16_t* split = at<uint16_t>(ws, L.split);
+    for (int j = top; j > base; --j) x = split[j * row + x] - 1;
+    at<uint16_t>(ws, L.jump)[(blockIdx.y + 1) * row + x0] = static_cast<uint16_t>(x);
+}
+
 // The last level (row b only, entry +1) and the backtrack, one workgroup. The path's rows
-// at the checkpoint levels come from anc and jump, one dependent read per kDpCheck levels;
+// at the checkpoint levels come from jump, one dependent read per kDpCheck levels;
 // then one lane per stretch between checkpoints walks its split entries, and the entries
 // (-1, +1 or the weighted mean of the interval) are formed in parallel: 32 dependent reads
 // at k = 256 where a walk along the levels took 255 (77-110 us). Degenerate histograms
@@ -768,8 +1123,15 @@ __global__ __launch_bounds__(1024) void k_dp_last(int32_t nbins, int32_t k, void
         *status = hdr[2];
         return;
     }
-    const size_t prev = ((keff - 1) & 1) * row;
-    const double* Dp = at<double>(ws, L.d) + prev;
+    if (hdr[5]) {   // a wait of k_dp_run ran out
+        for (int j = tid; j < k; j += 1024) codebook[j] = -1.0 + 2.0 * j / (k - 1);
+        if (tid == 0) {
+            *cost = INFINITY;
+            *status = 2;
+        }
+        return;
+    }
+    const double* Dp = at<double>(ws, L.d) + (keff - 1) * row;
     const double zr0 = Z0[b], zr1 = Z1[b], zr2 = Z2[b];
     double best = INFINITY;
     int arg = 0x7fffffff;
@@ -806,14 +1168,10 @@ __global__ __launch_bounds__(1024) void k_dp_last(int32_t nbins, int32_t k, void
         node[keff] = b;
         node[keff - 1] = a - 1;
         // checkpoint levels below keff - 1, multiples of kDpCheck
-        int lev = (keff - 2) / kDpCheck * kDpCheck;
-        if (lev > 0) {
-            int x = at<uint16_t>(ws, L.anc)[prev + a - 1];
-            node[lev] = x;
-            for (; lev > kDpCheck; lev -= kDpCheck) {
-                x = at<uint16_t>(ws, L.jump)[static_cast<size_t>(lev / kDpCheck) * row + x];
-                node[lev - kDpCheck] = x;
-            }
+        int x = a - 1;
+        for (int st = (keff - 2) / kDpCheck; st >= 1; --st) {
+            x = at<uint16_t>(ws, L.jump)[static_cast<size_t>(st) * row + x];
+            node[st * kDpCheck] = x;
         }
         node[0] = 0;
     }
@@ -946,13 +1304,20 @@ hipError_t launch_dp(const uint64_t* hist, int32_t nbins, int32_t k, void* ws,
                      double* codebook_out, double* cost_out, int32_t* status_out,
                      hipStream_t stream)
 {
-    hipLaunchKernelGGL(k_dp_prep, dim3(1), dim3(kThreads), 0, stream, hist, nbins, k, ws);
-    for (int j = 2; j < k; ++j) {
+    hipLaunchKernelGGL(k_dp_prep, dim3(1 + (k > kDpEntry ? kDpFill : 0)), dim3(kThreads), 0, stream,
+                       hist, nbins, k, ws);
+    for (int j = 2; j < k && j < kDpEntry; ++j) {
         // rows j .. nbins - k + j at most (b <= nbins, keff <= k; with b < k: rows j .. j)
         const int rows = nbins > k ? nbins - k + 1 : 1;
         hipLaunchKernelGGL(k_dp_level, dim3((rows + kDpRows - 1) / kDpRows), dim3(kDpThreads), 0,
                            stream, nbins, k, j, ws);
     }
+    if (k > kDpEntry)
+        hipLaunchKernelGGL(k_dp_run, dim3((nbins + kDpTile - 1) / kDpTile), dim3(kDpRunThreads), 0,
+                           stream, nbins, k, ws);
+    if (k - 2 >= kDpCheck)
+        hipLaunchKernelGGL(k_dp_jump, dim3(nbins / 256 + 1, (k - 2) / kDpCheck), dim3(256), 0,
+                           stream, nbins, k, ws);
     hipLaunchKernelGGL(k_dp_last, dim3(1), dim3(1024), 0, stream, nbins, k, ws, codebook_out,
                        cost_out, status_out);
     return hipGetLastError();

@@ -508,11 +508,11 @@ bool is_host_ptr(const void* p)
 
 // ------------------------------------------------------------------ fixed DP workspace
 // The workspace of gefen_dp_codebook_static: one array per GPU, for the process's
-// lifetime, large enough for the largest DP (16 * 256 bins, 256 entries: 2,510,080
+// lifetime, large enough for the largest DP (16 * 256 bins, 256 entries: 10,818,304
 // bytes). Host code never passes `scratch` itself to a kernel (in host code it is a
 // stand-in, not a device address): the first call on each device asks the runtime for
 // that device's copy and keeps the address.
-constexpr size_t kDpScratchBytes = size_t(3) << 20;
+constexpr size_t kDpScratchBytes = size_t(11) << 20;
 static __device__ __align__(256) unsigned char scratch[kDpScratchBytes];
 
 namespace {
