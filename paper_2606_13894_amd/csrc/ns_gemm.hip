@@ -40,12 +40,13 @@ __device__ __forceinline__ float bf16_val(uint16_t b)
     return __uint_as_float(static_cast<uint32_t>(b) << 16);
 }
 
-// float32 -> bfloat16, round to nearest even; NaN stays NaN.
-__device__ __forceinline__ uint16_t to_bf16(float x)
+// Two float32 -> bfloat16 in one conversion (round to nearest even; NaN stays NaN), low half first.
+__device__ __forceinline__ uint32_t to_bf16x2(float lo, float hi)
 {
-    const uint32_t b = __float_as_uint(x);
-    if ((b & 0x7fffffffu) > 0x7f800000u) return static_cast<uint16_t>((b >> 16) | 0x40u);
-    return static_cast<uint16_t>((b + 0x7FFFu + ((b >> 16) & 1u)) >> 16);
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    const f32x2 x = {lo, hi};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2));
 }
 
 // Element j (0..7) of eight packed bfloat16.
@@ -156,13 +157,10 @@ __device__ __forceinline__ void epilogue(
                     e[2] = bf16_val(static_cast<uint16_t>(ev.y & 0xffffu));
                     e[3] = bf16_val(static_cast<uint16_t>(ev.y >> 16));
                 }
-                uint32_t h[4];
+                float v[4];
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    h[q] = to_bf16(fmaf(a.alpha, acc[mi][ni][g * 4 + q], a.beta * e[q]));
-                u32x2 hv;
-                hv.x = h[0] | (h[1] << 16);
-                hv.y = h[2] | (h[3] << 16);
+                for (int q = 0; q < 4; ++q) v[q] = fmaf(a.alpha, acc[mi][ni][g * 4 + q], a.beta * e[q]);
+                const u32x2 hv = {to_bf16x2(v[0], v[1]), to_bf16x2(v[2], v[3])};
                 *cell = hv;
             }
         }
@@ -474,8 +472,7 @@ __global__ __launch_bounds__(256) void k_ns_reduce(const NsGemmArgs a)
     u32x4 h;
 #pragma unroll
     for (int c = 0; c < 4; ++c)
-        h[c] = uint32_t(to_bf16(a.alpha * v[2 * c])) |
-               (uint32_t(to_bf16(a.alpha * v[2 * c + 1])) << 16);
+        h[c] = to_bf16x2(a.alpha * v[2 * c], a.alpha * v[2 * c + 1]);
     if (i < a.M && j0 < a.o_cols)
         *reinterpret_cast<u32x4*>(a.o + w.b * a.so + i * a.ldo + j0) = h;
     if (w.ti == w.tj) return;
@@ -550,9 +547,8 @@ __global__ __launch_bounds__(256) void k_ns_prep(const uint16_t* __restrict__ sr
     for (int j = 0; j < 8; ++j)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const uint32_t lo = to_bf16(bf16_val(static_cast<uint16_t>(w[j][q] & 0xffffu)) / nrm);
-            const uint32_t hi = to_bf16(bf16_val(static_cast<uint16_t>(w[j][q] >> 16)) / nrm);
-            w[j][q] = lo | (hi << 16);
+            w[j][q] = to_bf16x2(bf16_val(static_cast<uint16_t>(w[j][q] & 0xffffu)) / nrm,
+                                bf16_val(static_cast<uint16_t>(w[j][q] >> 16)) / nrm);
         }
 #pragma unroll
     for (int j = 0; j < 8; ++j)

@@ -98,27 +98,40 @@ struct NsShape {
     int32_t tile_gram, tile_poly, tile_comb;
 };
 
-// Split the Gram product over K so that its workgroups (count x t (t + 1) / 2 upper
-// tiles, times the split) fill their rounds on the GPU: the smallest split whose rounds
-// are at least 90 % full, else the fullest, with chunks of at least 8 stages and at most
-// 32 chunks. A lone tall-skinny matrix (a token embedding: 21 small tiles at m = 768)
-// splits 22 ways; a batch that fills its rounds (the GPT-2 MLP group: 504 small tiles)
-// does not split.
-inline int32_t ns_gram_splits(int64_t count, int64_t m, int64_t ldx, int tile)
+// Estimated time of a Gram product in us: rounds of workgroups of kchunk / kNsBK stages each
+// (a stage of a pair of small tiles or of one big tile on a compute unit; a lone small tile's
+// takes less), start and epilogue, and for a split the float32 partials of the upper tiles,
+// written and read again, and the launch that adds them up. (Rates from the model shapes:
+// a split that only fills the rounds better does not pay for its partials. 6 x 2048 x 8192:
+// 216 big tiles on 256 units in one round 0.25 ms, split 3 ways 0.29 + 0.11 ms.)
+constexpr double kNsStageBigUs = 1.95, kNsStagePairUs = 1.7, kNsStageLoneUs = 1.2;
+constexpr double kNsTileUs = 9.0, kNsReduceUs = 6.0, kNsPartialBytesPerUs = 6.0e6;
+
+inline double ns_gram_us(int64_t count, int64_t m, int64_t ldx, int tile, int64_t splits)
 {
     const int64_t t = ns_tiles_along(m, tile);
-    const int64_t work = count * t * (t + 1) / 2;
+    const int64_t tiles = count * t * (t + 1) / 2, groups = tiles * splits;
+    const int64_t stages = (ldx / kNsBK + splits - 1) / splits;
+    const int64_t rounds = (groups + ns_slots(tile) - 1) / ns_slots(tile);
+    const double stage = tile == kNsTileBig ? kNsStageBigUs
+                         : groups <= kNsCUs ? kNsStageLoneUs : kNsStagePairUs;
+    double us = static_cast<double>(rounds) * (static_cast<double>(stages) * stage + kNsTileUs);
+    if (splits > 1)
+        us += kNsReduceUs + 2.0 * 4.0 * double(tile) * double(tile) * double(groups) /
+                                kNsPartialBytesPerUs;
+    return us;
+}
+
+// Split the Gram product over K (count x t (t + 1) / 2 upper tiles, times the split) where the
+// estimate says so, with chunks of at least 8 stages and at most 32 chunks. A lone tall-skinny
+// matrix (a token embedding: 21 small tiles at m = 768, 786 stages) splits 24 ways; a batch
+// that fills half its slots does not.
+inline int32_t ns_gram_splits(int64_t count, int64_t m, int64_t ldx, int tile)
+{
     const int64_t smax = std::max<int64_t>(1, std::min<int64_t>(32, ldx / (8 * kNsBK)));
     int64_t best = 1;
-    double best_fill = 0.0;
-    for (int64_t s = 1; s <= smax; ++s) {
-        const double fill = ns_fill(work * s, tile);
-        if (fill >= 0.9) return static_cast<int32_t>(s);
-        if (fill > best_fill + 1e-12) {
-            best = s;
-            best_fill = fill;
-        }
-    }
+    for (int64_t s = 2; s <= smax; ++s)
+        if (ns_gram_us(count, m, ldx, tile, s) < ns_gram_us(count, m, ldx, tile, best)) best = s;
     return static_cast<int32_t>(best);
 }
 
