@@ -16,6 +16,7 @@ Entry points mirror ``include/gefen.h``:
 """
 from __future__ import annotations
 
+import array
 import ctypes
 import os
 from typing import Optional, Sequence
@@ -114,38 +115,40 @@ def _check(rc: int):
         raise GefenError(rc, _lib.gefen_last_error().decode())
 
 
+_torch_module = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module
+    if _torch_module is None:   # imported on first use: loading the library needs no torch
+        import torch
+        _torch_module = torch
+    return _torch_module
 
 
 def _stream(stream=None):
-    torch = _torch()
-    s = stream if stream is not None else torch.cuda.current_stream()
+    s = stream if stream is not None else _torch().cuda.current_stream()
     return ctypes.c_void_p(s.cuda_stream)
 
 
-def _dtype_code(t) -> int:
-    torch = _torch()
-    if t.dtype == torch.float32:
-        return F32
-    if t.dtype == torch.bfloat16:
-        return BF16
-    raise TypeError(f"unsupported dtype {t.dtype}")
-
-
 def _tensors(ts: Sequence, what: str):
-    arr = (gefen_tensor * len(ts))()
+    """The gefen_tensor records of `ts`: three 64-bit words each (address, numel, then dtype
+    with the reserved word zero), packed in one go. Setting the fields one by one took about
+    2 us a tensor, more than the GPU needs for a small model's step."""
+    torch = _torch()
+    f32, bf16 = torch.float32, torch.bfloat16
+    words = array.array("q")
     for i, t in enumerate(ts):
         if not t.is_cuda:
             raise ValueError(f"{what}[{i}] must be a device tensor")
         if not t.is_contiguous():
             raise ValueError(f"{what}[{i}] must be contiguous")
-        arr[i].ptr = t.data_ptr()
-        arr[i].numel = t.numel()
-        arr[i].dtype = _dtype_code(t)
-        arr[i].reserved = 0
-    return arr
+        dt = t.dtype
+        if dt is not f32 and dt is not bf16:
+            raise TypeError(f"unsupported dtype {dt}")
+        words.extend((t.data_ptr(), t.numel(), F32 if dt is f32 else BF16))
+    rec = gefen_tensor * len(ts)
+    return rec.from_buffer(words) if words else rec()
 
 
 def _i64_array(vals):
@@ -185,6 +188,7 @@ class GefenState:
                               _stream(stream), ctypes.byref(out)))
         self._h = out
         del bo_np
+        self._layout = self._query_layout()   # fixed for the state's lifetime
 
     # --------------------------------------------------------------- lifecycle
     def close(self):
@@ -253,7 +257,7 @@ class GefenState:
         _check(_lib.gefen_get_periods(self._h, a))
         return list(a)
 
-    def layout(self):
+    def _query_layout(self):
         co = (ctypes.c_int64 * (self._n + 1))()
         bi = (ctypes.c_int64 * (self._n + 1))()
         cb, nb, k = ctypes.c_int64(), ctypes.c_int64(), ctypes.c_int32()
@@ -262,24 +266,33 @@ class GefenState:
         return {"code_offsets": list(co), "block_index": list(bi),
                 "code_bytes": cb.value, "total_blocks": nb.value, "k": k.value}
 
+    def layout(self):
+        if not self._h:
+            return self._query_layout()   # a closed state: the library's error
+        lay = dict(self._layout)
+        lay["code_offsets"] = list(lay["code_offsets"])
+        lay["block_index"] = list(lay["block_index"])
+        return lay
+
     @property
     def k(self) -> int:
-        return self.layout()["k"]
+        return self._layout["k"] if self._h else self._query_layout()["k"]
 
     def read(self, which: int, device=None, stream=None):
         """Copy a state array into a new tensor (device tensor by default)."""
         torch = _torch()
-        lay = self.layout()
-        spec = {STATE_CODES: (torch.uint8, lay["code_bytes"]),
-                STATE_SCALE: (torch.float32, lay["total_blocks"]),
-                STATE_V: (torch.float32, lay["total_blocks"]),
-                STATE_CB_DEC: (torch.float32, lay["k"]),
-                STATE_CB_ENC: (torch.float32, lay["k"]),
-                STATE_CB_DEC64: (torch.float64, lay["k"]),
-                STATE_MUON_U: (torch.int16, lay["code_offsets"][-1]),
-                STATE_HIST: (torch.int64, 16 * lay["k"])}[which]
-        dev = device if device is not None else torch.device("cuda", torch.cuda.current_device())
-        out = torch.empty(spec[1], dtype=spec[0], device=dev)
+        lay = self._layout
+        if which == STATE_CODES:
+            dtype, n = torch.uint8, lay["code_bytes"]
+        elif which in (STATE_SCALE, STATE_V):
+            dtype, n = torch.float32, lay["total_blocks"]
+        else:
+            dtype, n = {STATE_CB_DEC: (torch.float32, lay["k"]),
+                        STATE_CB_ENC: (torch.float32, lay["k"]),
+                        STATE_CB_DEC64: (torch.float64, lay["k"]),
+                        STATE_MUON_U: (torch.int16, lay["code_offsets"][-1]),
+                        STATE_HIST: (torch.int64, 16 * lay["k"])}[which]
+        out = torch.empty(n, dtype=dtype, device="cuda" if device is None else device)
         nbytes = out.numel() * out.element_size()
         _check(_lib.gefen_read_state(self._h, int(which), ctypes.c_void_p(out.data_ptr()),
                                      nbytes, _stream(stream)))
