@@ -342,7 +342,7 @@ int gefen_muon_profile_end(gefen_state* st, int32_t* steps, double* codec_ms, do
  *         at x_in + b * m * n, 1 <= m <= n <= 2^31 - 4096, batch in [1, 65535].
  *  x_out  device uint16[batch * m * n], same layout; may equal x_in.
  *  steps  in [0, 100] (0 copies x_in to x_out); a, b, c finite.
- * Asynchronous on `stream`; its workspace (about 8 bytes per element of the batch) is
+ * Asynchronous on `stream`; its workspace (4 to 6 bytes per element of the batch) is
  * allocated and freed stream-ordered on `stream`.
  * Errors: EINVAL (NULL, sizes, steps, coefficients), ENOMEM, EHIP.
  * ---------------------------------------------------------------------------- */

@@ -1162,12 +1162,16 @@ float host_bf16_value(float x)
 // One Newton-Schulz iteration of a shape group on a lane's buffers (ns_plan.h):
 // A = X X^T, B = b A + c A A, X' = a X + B X, each a bfloat16 product with float32
 // accumulation; `cur` selects the ping-pong buffers that hold X and X^T.
+// After the last iteration only the orientations that are read need to be written.
 int ns_iteration(const NsLaneBuffers& lb, const NsLaneSizes& z, const NsShape& sh, int cur,
-                 float a, float b, float c, hipStream_t stream)
+                 float a, float b, float c, hipStream_t stream, bool want_x = true,
+                 bool want_xt = true)
 {
     NsGemmArgs prods[3];
     int64_t avail[3][6];
     ns_iteration_products(sh, lb, z, cur, a, b, c, prods, avail);
+    if (!want_x) prods[2].o = nullptr;
+    if (!want_xt) prods[2].ot = nullptr;
     for (const NsGemmArgs& p : prods) GEFEN_HIP(launch_ns_gemm(p, stream));
     return GEFEN_OK;
 }
@@ -1238,10 +1242,11 @@ int muon_lane_resources(gefen_state* st)
         if (ln.groups.empty()) continue;
         ln.size = ns_lane_sizes(st->muon_groups, ln.groups);
         NsLaneBuffers& lb = ln.buf;
-        for (int k = 0; k < 2; ++k) {
-            if ((rc = st->alloc(&lb.x[k], 2 * static_cast<size_t>(ln.size.x_elems), false))) return rc;
+        // one X: only the Gram product reads it, before the combine writes the next one
+        if ((rc = st->alloc(&lb.x[0], 2 * static_cast<size_t>(ln.size.x_elems), false))) return rc;
+        lb.x[1] = lb.x[0];
+        for (int k = 0; k < 2; ++k)
             if ((rc = st->alloc(&lb.xt[k], 2 * static_cast<size_t>(ln.size.x_elems), false))) return rc;
-        }
         if ((rc = st->alloc(&lb.a, 2 * static_cast<size_t>(ln.size.a_elems), false))) return rc;
         if ((rc = st->alloc(&lb.b, 2 * static_cast<size_t>(ln.size.a_elems), false))) return rc;
         if ((rc = st->alloc(&lb.partial, 4 * static_cast<size_t>(ln.size.partial_elems), false)))
@@ -1293,7 +1298,8 @@ int muon_group_phase(gefen_state* st, const gefen_state::MuonLane& lane, const N
             uint16_t* t0 = ln.xt[0] + pt.first * ts;
             if (sh.m == 1)
                 GEFEN_HIP(launch_ns_prep(st->muon_u, st->muon_u_off, tof, st->muon_norm, pt.count,
-                                         1, pt.rows * pt.cols, x0, xs, sh.ldx, t0, ts, sh.ldm, ls));
+                                         1, pt.rows * pt.cols, x0, xs, sh.ldx, nullptr, ts, sh.ldm,
+                                         ls));
             else if (!pt.transposed)
                 GEFEN_HIP(launch_ns_prep(st->muon_u, st->muon_u_off, tof, st->muon_norm, pt.count,
                                          pt.rows, pt.cols, x0, xs, sh.ldx, t0, ts, sh.ldm, ls));
@@ -1306,7 +1312,9 @@ int muon_group_phase(gefen_state* st, const gefen_state::MuonLane& lane, const N
             GEFEN_HIP(launch_muon_ns_vec(ln.x[0], static_cast<int32_t>(sh.count), sh.n, sh.ldx,
                                          r.ns_steps, r.ca, r.cb, r.cc, ls));
         } else {
-            const int rc = ns_iteration(ln, lane.size, sh, cur, r.ca, r.cb, r.cc, ls);
+            bool wide = phase + 1 < last, tall = wide;   // the last: what the updates read
+            for (const auto& pt : g.parts) (pt.transposed ? tall : wide) = true;
+            const int rc = ns_iteration(ln, lane.size, sh, cur, r.ca, r.cb, r.cc, ls, wide, tall);
             if (rc) return rc;
             cur ^= 1;
         }
@@ -1513,10 +1521,22 @@ int gefen_newton_schulz(const uint16_t* x_in, uint16_t* x_out, int32_t batch, in
         return GEFEN_OK;
     };
     int rc;
-    for (int k = 0; k < 2; ++k) {
-        if ((rc = get(reinterpret_cast<void**>(&lb.x[k]), 2 * z.x_elems))) return rc;
+    // Where a dense matrix has X's layout, X is x_in until the first combine and x_out from
+    // then on (only the Gram product reads X, before the combine writes it); else a padded
+    // buffer, as for inputs that overlap the output in part.
+    const int64_t bytes = 2 * static_cast<int64_t>(batch) * m * n;
+    const auto gap = reinterpret_cast<intptr_t>(x_out) - reinterpret_cast<intptr_t>(x_in);
+    const bool direct = m > 1 && sh.ldx == n && steps > 0 &&
+                        ((reinterpret_cast<uintptr_t>(x_in) | reinterpret_cast<uintptr_t>(x_out)) &
+                         15) == 0 &&
+                        (gap == 0 || gap >= bytes || -gap >= bytes);
+    if (direct)
+        lb.x[0] = x_out;
+    else if ((rc = get(reinterpret_cast<void**>(&lb.x[0]), 2 * z.x_elems)))
+        return rc;
+    lb.x[1] = lb.x[0];
+    for (int k = 0; k < 2 && m > 1; ++k)
         if ((rc = get(reinterpret_cast<void**>(&lb.xt[k]), 2 * z.x_elems))) return rc;
-    }
     if ((rc = get(reinterpret_cast<void**>(&lb.a), 2 * z.a_elems))) return rc;
     if ((rc = get(reinterpret_cast<void**>(&lb.b), 2 * z.a_elems))) return rc;
     if ((rc = get(reinterpret_cast<void**>(&lb.partial), 4 * z.partial_elems))) return rc;
@@ -1529,21 +1549,25 @@ int gefen_newton_schulz(const uint16_t* x_in, uint16_t* x_out, int32_t batch, in
     }
     const int64_t xs = sh.m * sh.ldx, ts = sh.ldx * sh.ldm;
     auto run = [&]() -> int {
-        GEFEN_HIP(launch_ns_prep(x_in, nullptr, nullptr, nullptr, batch, m, n, lb.x[0], xs,
-                                 sh.ldx, lb.xt[0], ts, sh.ldm, stream));
+        GEFEN_HIP(launch_ns_prep(x_in, nullptr, nullptr, nullptr, batch, m, n,
+                                 direct ? nullptr : lb.x[0], xs, sh.ldx,
+                                 m > 1 ? lb.xt[0] : nullptr, ts, sh.ldm, stream));
         int cur = 0;
         if (m == 1) {
             GEFEN_HIP(launch_muon_ns_vec(lb.x[0], batch, n, sh.ldx, steps, static_cast<float>(a),
                                          static_cast<float>(b), static_cast<float>(c), stream));
         } else {
             for (int32_t it = 0; it < steps; ++it) {
-                const int r = ns_iteration(lb, z, sh, cur, static_cast<float>(a),
-                                           static_cast<float>(b), static_cast<float>(c), stream);
+                NsLaneBuffers at = lb;
+                if (direct && it == 0) at.x[cur] = const_cast<uint16_t*>(x_in);
+                const int r = ns_iteration(at, z, sh, cur, static_cast<float>(a),
+                                           static_cast<float>(b), static_cast<float>(c), stream,
+                                           true, it + 1 < steps);
                 if (r) return r;
                 cur ^= 1;
             }
         }
-        GEFEN_HIP(launch_ns_unpad(lb.x[cur], xs, sh.ldx, batch, m, n, x_out, stream));
+        if (!direct) GEFEN_HIP(launch_ns_unpad(lb.x[cur], xs, sh.ldx, batch, m, n, x_out, stream));
         return GEFEN_OK;
     };
     rc = run();
