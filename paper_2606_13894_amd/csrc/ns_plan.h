@@ -140,12 +140,12 @@ inline int32_t ns_gram_splits(int64_t count, int64_t m, int64_t ldx, int tile)
 // rounds; else the small tile. (Measured on the model shapes: at M = 768 the small tile
 // is faster for every product -- the MLP combine 186 against 231 us, the Gram 72 against
 // 154 us with its split -- and at M = 2048 the big one by about 8 %.)
-inline int ns_pick_tile(int64_t count, int64_t M, int64_t N, bool sym, int32_t splits = 1)
+inline int ns_pick_tile(int64_t count, int64_t M, int64_t N, bool sym)
 {
     if (M < 4 * kNsTileBig || N < 4 * kNsTileBig) return kNsTileSmall;
     const int64_t tm = ns_tiles_along(M, kNsTileBig), tn = ns_tiles_along(N, kNsTileBig);
     const int64_t tiles = sym ? tm * (tm + 1) / 2 : tm * tn;
-    return ns_fill(count * tiles * splits, kNsTileBig) >= 0.75 ? kNsTileBig : kNsTileSmall;
+    return ns_fill(count * tiles, kNsTileBig) >= 0.75 ? kNsTileBig : kNsTileSmall;
 }
 
 inline NsShape ns_shape(int64_t count, int64_t m, int64_t n)
@@ -154,10 +154,17 @@ inline NsShape ns_shape(int64_t count, int64_t m, int64_t n)
               kNsTileSmall, kNsTileSmall};
     s.kchunk = static_cast<int32_t>(s.ldx);
     if (m < 2) return s;   // vectors have no matrix products
-    // the Gram product: the big tile when it fills the GPU with its own best split
-    const int32_t sb = ns_gram_splits(count, m, s.ldx, kNsTileBig);
-    s.tile_gram = ns_pick_tile(count, m, m, true, sb);
-    s.splits = s.tile_gram == kNsTileBig ? sb : ns_gram_splits(count, m, s.ldx, kNsTileSmall);
+    // the Gram product: the tile whose estimate with its own best split is lower (3 x 1500 x
+    // 2113: 78 small tiles a matrix unsplit 32 us, 21 big ones split 4 ways 30 + 17 us)
+    s.splits = ns_gram_splits(count, m, s.ldx, kNsTileSmall);
+    if (m >= 4 * kNsTileBig) {
+        const int32_t sb = ns_gram_splits(count, m, s.ldx, kNsTileBig);
+        if (ns_gram_us(count, m, s.ldx, kNsTileBig, sb) <
+            ns_gram_us(count, m, s.ldx, kNsTileSmall, s.splits)) {
+            s.tile_gram = kNsTileBig;
+            s.splits = sb;
+        }
+    }
     if (s.splits > 1) {
         // equal chunks of whole stages; the last one may be shorter, none is empty
         const int64_t chunk = (s.ldx + s.splits - 1) / s.splits;
