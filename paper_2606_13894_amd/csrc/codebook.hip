@@ -462,13 +462,14 @@ __device__ __forceinline__ bool dp_may_prune(double total, int32_t nbins)
 
 // Compaction of non-empty bins and prefix sums, in increasing bin order. The workgroup
 // compacts the non-empty bins (a prefix count over 16-bin runs) and forms each one's
-// centre, count and the two products c m and (c m) m in LDS; three threads, one wave each,
-// then take a running sum each in increasing bin order, sixteen terms loaded ahead of
-// their additions, so the summation order is the definition's. The chain of 4096 dependent
-// float64 additions bounds the kernel (one thread taking all three, term by term: 155 us).
+// centre, count and the two products c m and (c m) m in LDS; three waves then take a running
+// sum each in increasing bin order, so the summation order is the definition's. A wave holds
+// 64 terms in its lanes and adds them one after another from scalar registers. The chain of
+// 4096 dependent float64 additions bounds the kernel: 65 us; 82 us with one lane that reads
+// and writes its terms in LDS sixteen at a time, 155 us with one thread for all three sums.
 // Level 1 (one interval, entry -1) is written on the way out.
 constexpr int kPrepRun = kMaxBins / kThreads;   // bins per thread in the compaction
-constexpr int kPrepBatch = 16;
+constexpr int kPrepBatch = 64;
 
 __global__ __launch_bounds__(kThreads) void k_dp_prep(const uint64_t* __restrict__ hist,
                                                       int32_t nbins, int32_t k, void* ws)
@@ -537,27 +538,23 @@ __global__ __launch_bounds__(kThreads) void k_dp_prep(const uint64_t* __restrict
     if (tid < 3) t[tid][0] = 0.0;
     if (tid < 3 * kPrepBatch) t[tid / kPrepBatch][b + 1 + tid % kPrepBatch] = 0.0;
     __syncthreads();
-    if ((tid & 63) == 0 && tid < 192) {
+    if (tid < 192) {   // wave q: 64 terms in its lanes, added one after another
         double* __restrict__ x = t[tid >> 6];
-        double z = 0.0;
-        double next[kPrepBatch];
-#pragma unroll
-        for (int u = 0; u < kPrepBatch; ++u) next[u] = x[1 + u];
-        for (int q = 1; q <= b; q += kPrepBatch) {
-            double cur[kPrepBatch];
-#pragma unroll
-            for (int u = 0; u < kPrepBatch; ++u) cur[u] = next[u];
-            // the batch after this one: x has kPrepBatch slots past b + kPrepBatch - 1
-            const int ahead = q + kPrepBatch <= b ? q + kPrepBatch : q;
-#pragma unroll
-            for (int u = 0; u < kPrepBatch; ++u) next[u] = x[ahead + u];
+        const int lane = tid & 63;
+        double z = 0.0, next = x[1 + lane];
+        for (int q = 0; q < b; q += kPrepBatch) {
+            const double term = next;
+            next = x[q + kPrepBatch + 1 + lane];   // x has 2 kPrepBatch slots past kMaxBins
+            double keep = 0.0;
 #pragma unroll
             for (int u = 0; u < kPrepBatch; ++u) {
-                z = z + cur[u];
-                cur[u] = z;
+                const uint64_t w = __builtin_bit_cast(uint64_t, term);
+                const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(w), u);
+                const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(w >> 32), u);
+                z = z + __builtin_bit_cast(double, (static_cast<uint64_t>(hi) << 32) | lo);
+                keep = lane == u ? z : keep;
             }
-#pragma unroll
-            for (int u = 0; u < kPrepBatch; ++u) x[q + u] = cur[u];
+            x[q + 1 + lane] = keep;
         }
     }
     __syncthreads();
