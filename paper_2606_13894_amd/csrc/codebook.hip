@@ -634,11 +634,11 @@ __device__ __forceinline__ double wave_min(double v)
 // lies within slack of the minimum; a row that the level before did not have takes the
 // from of the row below it. Values and argmins are those of the full scan, bit for bit.
 //
-// The candidates fall from 1.9e9 to 5e7 at b = 4096, k = 256 (windows of 14 to 40 bins from
-// level 64 on), and a level is bound by its launch and two dependent trips to memory: the
-// first 64 candidates are loaded before the header and the lower bound are known. Full
-// scan, with the candidates staged in LDS, took 18.1 us a level; this takes 4.4-5.6 us from
-// level 16 on (30 us at level 2): 1.38 against 4.82 ms for the whole DP.
+// The candidates fall from 1.9e9 to 5e7 at b = 4096, k = 256, and a level is bound by its
+// launch and two dependent trips to memory, at the first levels by long windows too: the
+// first 64 candidates are loaded before the header and the lower bound are known (loading
+// four or eight chunks ahead as well changed nothing). 30, 23, 13, 10, 9 and 9 us for the
+// levels 2 to 7; 18.1 us a level for the full scan with the candidates staged in LDS.
 // ---------------------------------------------------------------------------------
 __global__ __launch_bounds__(kDpThreads) void k_dp_level(int32_t nbins, int32_t k, int32_t j,
                                                          void* ws)
