@@ -624,15 +624,24 @@ __device__ __forceinline__ double wave_min(double v)
 //       optimal path of j - 1 edges to y and one of j edges to x < y: an edge of the second
 //       lies inside one of the first, and exchanging the two paths' tails there gives j
 //       edges to y and j - 1 to x at no higher cost.)
-// So a candidate that is worse than another by more than the rounding of both stays worse
-// at all higher levels and rows, and is never the computed minimum there. Rounding: the
-// computed C is off by at most 7.2 u (S2 + S1^2 / S0), u = 2^-53, and at most 12.1 u S0 in
-// the forced interval; along a path the intervals are disjoint, so these add up to less
-// than 28 u Z0[r], and each level adds at most 1.1 u of the value itself. A difference of
-// computed candidates is therefore within u (112 Z0[r] + 10 k D) of the exact one over two
+// So a candidate l' that is worse than the minimum, at l, by more than the rounding of both
+// stays worse than l's at all higher levels and rows, and is never the computed minimum
+// there. Rounding: the computed C is off by at most 7.2 u (S2 + S1^2 / S0), u = 2^-53, and
+// at most 12.1 u S0 in the forced interval; along a path the intervals are disjoint, so these
+// add up to less than 28 u Z0[r], and each level adds at most 1.1 u of the value itself. At
+// a higher level l's value is no larger than at this one (its D is not), so a difference of
+// computed candidates of row r is within u (112 Z0[r] + 10 k D) of the exact one over two
 // levels; `slack` is about twice that. from[r] = the smallest l whose computed candidate
-// lies within slack of the minimum; a row that the level before did not have takes the
-// from of the row below it. Values and argmins are those of the full scan, bit for bit.
+// lies within slack of the minimum.
+//
+// A row that the level before did not have takes the from of the row below it, so that
+// bound is handed from row to row and has to hold with the rounding of all the rows still
+// to come. There Z0 is at most Z0[b]; l's value exceeds the one here by at most Z2[b], once
+// (its D is still this row's), and the D before l' is no larger than the one before l. So
+// the level's last row, which hands its bound on, takes the slack with Z0[b] for Z0[r]. (With
+// Z0[r] a bin of 2e10 counts above rows of a few counts each moved entries by 1e-3.)
+//
+// Values and argmins are those of the full scan, bit for bit.
 //
 // The candidates fall from 1.9e9 to 5e7 at b = 4096, k = 256, and a level is bound by its
 // launch and two dependent trips to memory, at the first levels by long windows too: the
@@ -687,8 +696,9 @@ __global__ __launch_bounds__(kDpThreads) void k_dp_level(int32_t nbins, int32_t 
         }
     }
     const double m = wave_min(best);
+    const double zs0 = r < rmax ? zr0 : Z0[b];   // the last row's bound is handed on
     const double slack = 1.1102230246251565e-16 *
-                         (256.0 * zr0 + 32.0 * static_cast<double>(k) * m);
+                         (256.0 * zs0 + 32.0 * static_cast<double>(k) * m);
     const double near = m + slack;
     int bestl, from;
     if (!(m < INFINITY)) {   // no candidate has a value (see above)
@@ -837,6 +847,7 @@ __global__ __launch_bounds__(kDpRunThreads) void k_dp_run(int32_t nbins, int32_t
     __syncthreads();
     const int b = hdr[0], keff = hdr[1];
     const bool prune = hdr[3] != 0;
+    const double total = at<double>(ws, L.z0)[b];
     const int R0 = 1 + tile_s * kDpTile;
     // rows [j, b - keff + j] at level j: the first level with a row of this tile
     const int lift = b - keff;
@@ -919,7 +930,9 @@ __global__ __launch_bounds__(kDpRunThreads) void k_dp_run(int32_t nbins, int32_t
         int hi = 0x7fffffff;   // no row needs a candidate above
         const double zr0 = zs[0][r], zr1 = zs[1][r], zr2 = zs[2][r];
         const double slack1 = 1.1102230246251565e-16 * 32.0 * static_cast<double>(k);
-        const double slack0 = minima ? 1.1102230246251565e-16 * 256.0 * zs[0][cr] : 0.0;
+        // of the level's last row with the total count (k_dp_level)
+        const double slack0 =
+            minima ? 1.1102230246251565e-16 * 256.0 * (cr < rmax ? zs[0][cr] : total) : 0.0;
         auto candidates = [&](int c0) {
             const int l = lq + c0 + slot;
             double c = INFINITY;
@@ -992,7 +1005,8 @@ __global__ __launch_bounds__(kDpRunThreads) void k_dp_run(int32_t nbins, int32_t
             lds_barrier();
             const double mt = row_min(wmin[lane & 7]);
             const double mh = row_min(whigh[lane & 7]);
-            const double neart = mt + (1.1102230246251565e-16 * 256.0 * t0 + slack1 * mt);
+            const double neart =
+                mt + (1.1102230246251565e-16 * 256.0 * (rt < rmax ? t0 : total) + slack1 * mt);
             if (mh > neart) {
                 if (minima) reduce(0, kDpEach / 2, true, true);
                 done = true;

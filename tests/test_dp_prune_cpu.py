@@ -3,10 +3,12 @@ oracle's full scan.
 
 The library's DP looks, for row r of level j, only at the candidates l from the smallest l
 that came within a rounding slack of the row's minimum one level below (the quadrangle
-inequality of the interval costs keeps every smaller l worse from then on). This test
-restates that rule in numpy, float64 operations in the oracle's order, and checks codebook,
-cost and interval starts bit for bit, on histograms with many exact ties, plateaus beside
-spikes of 1e9, and empty stretches."""
+inequality of the interval costs keeps every smaller l worse from then on). A level's last
+row hands its bound to the rows that later levels add, so its slack is that of the total
+count. This test restates that rule in numpy, float64 operations in the oracle's order, and
+checks codebook, cost and interval starts bit for bit, on histograms with many exact ties,
+plateaus beside spikes of 1e9, empty stretches, and a few counts a bin below bins of 2e10 to
+1e11 (where a slack of the handing row's own count drops candidates that win)."""
 import numpy as np
 import pytest
 
@@ -38,7 +40,7 @@ def pruned_dp(hist, k):
             cand = d[l - 1] + w
             i = int(np.argmin(cand))
             new[r], split[j, r] = cand[i], lo + i
-            slack = 2.0 ** -53 * (256.0 * z0[r] + 32.0 * k * cand[i])
+            slack = 2.0 ** -53 * (256.0 * (z0[b] if r == rmax else z0[r]) + 32.0 * k * cand[i])
             nlow[r] = lo + int(np.argmax(cand <= cand[i] + slack))
             seen += l.size
         d, low = new, nlow
@@ -77,6 +79,18 @@ def histogram(kind, nbins, seed):
     return h
 
 
+def heavy_top(nbins, k, fill, seed, big):
+    """1 to 3 counts in each of the last `fill` bins, but `big` in two of the last k."""
+    rng = np.random.default_rng(seed)
+    h = np.zeros(nbins, dtype=np.uint64)
+    h[nbins - fill:] = rng.integers(1, 4, fill).astype(np.uint64)
+    h[nbins - 2 - rng.integers(0, min(k, fill) - 4, 2)] = big
+    return h
+
+
+# (nbins, k, fill, seed, big)
+HEAVY = [(4096, 64, 80, 14, 5 * 10 ** 10), (4096, 64, 80, 11, 2 * 10 ** 10),
+         (4096, 256, 300, 3, 10 ** 11)]
 KINDS = ["bell", "flat", "spikes", "centre", "two_scales", "comb", "gaps"]
 
 
@@ -92,6 +106,17 @@ def test_pruned_scan_equals_the_full_scan(kind, nbins, k):
     np.testing.assert_array_equal(bounds, bounds_ref)
     b = int(np.count_nonzero(h))
     assert seen < sum(r - j + 1 for j in range(2, k) for r in range(j, b - k + j + 1)) + b
+
+
+@pytest.mark.parametrize("nbins,k,fill,seed,big", HEAVY)
+def test_bounds_handed_past_heavy_bins(nbins, k, fill, seed, big):
+    h = heavy_top(nbins, k, fill, seed, big)
+    cb, cost, bounds, _ = pruned_dp(h, k)
+    cb_ref, cost_ref, bounds_ref, st = oracle.dp_codebook(h, k)
+    assert st == 0
+    np.testing.assert_array_equal(cb, cb_ref)
+    assert cost == cost_ref
+    np.testing.assert_array_equal(bounds, bounds_ref)
 
 
 def test_prefix_sums_are_sequential():

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 import oracle
-from test_dp_prune_cpu import KINDS, histogram
+from test_dp_prune_cpu import HEAVY, KINDS, heavy_top, histogram
 
 
 def bounded_dp(hist, k, tile):
@@ -37,7 +37,8 @@ def bounded_dp(hist, k, tile):
             cand = d[l - 1] + w
             i = int(np.argmin(cand))
             new[r], split[j, r] = cand[i], lo + i
-            near = np.nonzero(cand <= cand[i] + 2.0 ** -53 * (256.0 * z0[r] + 32.0 * k * cand[i]))[0]
+            slack = 2.0 ** -53 * (256.0 * (z0[b] if r == rmax else z0[r]) + 32.0 * k * cand[i])
+            near = np.nonzero(cand <= cand[i] + slack)[0]
             nlow[r] = lo + int(near[0])
             if top:
                 hi = lo + int(near[-1])
@@ -66,3 +67,14 @@ def test_bounded_scan_equals_the_full_scan(kind, nbins, k, tile):
     np.testing.assert_array_equal(bounds, bounds_ref)
     if kind == "bell":
         assert cut > 0
+
+
+@pytest.mark.parametrize("nbins,k,fill,seed,big", HEAVY)
+def test_bounds_handed_past_heavy_bins(nbins, k, fill, seed, big):
+    h = heavy_top(nbins, k, fill, seed, big)
+    cb, cost, bounds, _ = bounded_dp(h, k, 16)
+    cb_ref, cost_ref, bounds_ref, st = oracle.dp_codebook(h, k)
+    assert st == 0
+    np.testing.assert_array_equal(cb, cb_ref)
+    assert cost == cost_ref
+    np.testing.assert_array_equal(bounds, bounds_ref)

@@ -7,7 +7,7 @@ import pytest
 import torch
 
 import oracle
-from test_dp_prune_cpu import KINDS, histogram
+from test_dp_prune_cpu import HEAVY, KINDS, heavy_top, histogram
 
 pytestmark = pytest.mark.gpu
 
@@ -26,6 +26,29 @@ def _check(h, k):
 @pytest.mark.parametrize("nbins,k", [(4096, 256), (1000, 34), (256, 16)])
 def test_dp_kinds(kind, nbins, k):
     _check(histogram(kind, nbins, seed=nbins + 7 * k), k)
+
+
+@pytest.mark.parametrize("nbins,k,fill,seed,big", HEAVY)
+def test_dp_heavy_bins(nbins, k, fill, seed, big):
+    """Rows that later levels add, with far larger sums than the row whose bound they take."""
+    _check(heavy_top(nbins, k, fill, seed, big), k)
+
+
+@pytest.mark.parametrize("seed", range(40))
+def test_dp_random_spikes(seed):
+    """A few counts a bin beside up to four bins near the largest counts that still prune."""
+    rng = np.random.default_rng(seed)
+    nbins, k = int(rng.choice([256, 1024, 4096])), int(rng.choice([9, 16, 33, 64, 100]))
+    fill = int(rng.integers(k + 2, 250))
+    at = [np.arange(nbins - fill, nbins), np.arange(fill),
+          np.sort(rng.choice(nbins, fill, replace=False))][seed % 3]
+    h = np.zeros(nbins, dtype=np.uint64)
+    h[at] = rng.integers(1, 4, fill).astype(np.uint64)
+    n = int(rng.integers(1, 5))
+    most = 0.9 * 2.0 ** 50 / nbins / n
+    for _ in range(n):
+        h[at[rng.integers(0, fill)]] = int(min(most, 10 ** rng.uniform(8, np.log10(most))))
+    _check(h, k)
 
 
 @pytest.mark.parametrize("k", [2, 3, 16, 17, 18, 19, 32, 33, 34, 50])
