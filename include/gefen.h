@@ -173,8 +173,7 @@ int gefen_histogram(gefen_state* st, const gefen_tensor* grads, int32_t n_tensor
  * uint64[nbins]) into k sorted entries with the first forced to -1 and the last to
  * +1. Outputs: codebook_out device double[k], cost_out device double[1],
  * status_out device int32[1] (0 ok, 1 degenerate: fewer non-empty bins than k, the
- * DP then uses max(b, 2) entries and pads with +1; 2 the bounded wait between the DP's
- * row tiles ran out: cost infinite, uniform entries). Asynchronous; its workspace is
+ * DP then uses max(b, 2) entries and pads with +1). Asynchronous; its workspace is
  * allocated and freed stream-ordered on `stream`.
  * Errors: EINVAL (NULL pointer, k outside [2, 256], nbins outside [1, 4096]), EHIP. */
 int gefen_dp_codebook(const uint64_t* hist, int32_t nbins, int32_t k, double* codebook_out,
@@ -234,7 +233,7 @@ int gefen_write_state(gefen_state* st, int32_t which, const void* src, int64_t b
                       void* stream);
 
 /* Result of the last codebook fit (init or gefen_fit_codebook): DP cost and
- * status (as gefen_dp_codebook). Either output may be NULL. Synchronises `stream`.
+ * status (0 ok, 1 degenerate). Either output may be NULL. Synchronises `stream`.
  * Errors: EINVAL (NULL state), EHIP. */
 int gefen_get_fit_info(const gefen_state* st, double* cost_out, int32_t* status_out,
                        void* stream);

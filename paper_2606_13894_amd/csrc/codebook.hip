@@ -750,7 +750,7 @@ __global__ __launch_bounds__(kDpThreads) void k_dp_level(int32_t nbins, int32_t 
 // which the workgroups start, so whoever a workgroup waits for has started and itself waits
 // for nothing higher: no assumption on residency or dispatch order is needed. Waits are
 // bounded all the same (kDpSpin polls, seconds); one that runs out ends its workgroup, and
-// k_dp_last reports it as status 2 with the uniform codebook.
+// k_dp_last then computes these levels itself (dp_levels_alone).
 //
 // Lower bounds, candidates, slack and tie rules are k_dp_level's. A lane takes a row and one
 // of its candidates, kDpChunk of them from the row's lower bound up, into `cand`; after a
@@ -783,7 +783,6 @@ constexpr int kDpWaves = kDpRunThreads / 64;
 constexpr int kDpChunk = kDpRunThreads / kDpTile;   // candidates of a row at once
 constexpr int kDpEach = kDpChunk / 16;              // of one lane in the minimum
 constexpr int kDpPitch = kDpTile + 1;   // doubles; a row's candidates hit distinct banks
-constexpr int kDpSpin = 1 << 20;
 
 // Workgroup barrier for LDS only: global loads and stores stay in flight.
 __device__ __forceinline__ void lds_barrier()
@@ -820,7 +819,9 @@ __device__ __forceinline__ int row_imin(int v)
     return dpp_imin<0x140>(v);
 }
 
-__global__ __launch_bounds__(kDpRunThreads) void k_dp_run(int32_t nbins, int32_t k, void* ws)
+// `polls`: of one wait, at most (negative: every tile ends at its first level).
+__global__ __launch_bounds__(kDpRunThreads) void k_dp_run(int32_t nbins, int32_t k, int32_t polls,
+                                                          void* ws)
 {
     __shared__ double zs[3][kMaxBins + 1];
     __shared__ double ds[kMaxBins + 1];
@@ -839,7 +840,7 @@ __global__ __launch_bounds__(kDpRunThreads) void k_dp_run(int32_t nbins, int32_t
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (tid == 0) {   // the tile in order of the workgroups' starts
         tile_s = atomicAdd(&hdr[4], 1);
-        dead = 0;
+        dead = polls < 0;
         wide[0] = wide[1] = 0;
         low[0] = low[1] = reach[0] = reach[1] = first_in = 0x7fffffff;
         last_in = -1;
@@ -899,7 +900,7 @@ __global__ __launch_bounds__(kDpRunThreads) void k_dp_run(int32_t nbins, int32_t
                 for (int spin = 0; v == kDpUnset; ++spin) {
                     v = dp_load(Dp + x);
                     if (v != kDpUnset) break;
-                    if (spin == kDpSpin) {
+                    if (spin >= polls) {
                         dead = 1;
                         break;
                     }
@@ -1097,6 +1098,49 @@ __global__ __launch_bounds__(256) void k_dp_jump(int32_t nbins, int32_t k, void*
     at<uint16_t>(ws, L.jump)[(blockIdx.y + 1) * row + x0] = static_cast<uint16_t>(x);
 }
 
+// Levels kDpEntry .. keff - 1 by one workgroup of 1024, every candidate of every row, where a
+// wait of k_dp_run ran out (by reading it never does): the same values and argmins, about
+// half a second at 4096 bins and 256 entries.
+__device__ __forceinline__ void dp_levels_alone(int32_t nbins, int32_t k, int32_t b, int32_t keff,
+                                             void* ws)
+{
+    const DpLayout L = dp_layout(nbins, k);
+    const size_t row = static_cast<size_t>(nbins) + 1;
+    const double* Z0 = at<double>(ws, L.z0);
+    const double* Z1 = at<double>(ws, L.z1);
+    const double* Z2 = at<double>(ws, L.z2);
+    double* D = at<double>(ws, L.d);
+    uint16_t* split = at<uint16_t>(ws, L.split);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int j = kDpEntry; j < keff; ++j) {
+        const double* Dp = D + (j - 1) * row;
+        for (int r = j + wave; r <= b - keff + j; r += 1024 / 64) {
+            const double zr0 = Z0[r], zr1 = Z1[r], zr2 = Z2[r];
+            double best = INFINITY;
+            int arg = 0x7fffffff;
+            for (int l = j + lane; l <= r; l += 64) {   // rising l: the first minimum kept
+                const double c = Dp[l - 1] + dp_cost_free(zr0, zr1, zr2, Z0[l - 1], Z1[l - 1],
+                                                          Z2[l - 1]);
+                if (c < best) {
+                    best = c;
+                    arg = l;
+                }
+            }
+            const double m = wave_min(best);
+            if (best != m) arg = 0x7fffffff;
+            for (int off = 1; off < 64; off <<= 1) {
+                const int o = __shfl_xor(arg, off);
+                arg = o < arg ? o : arg;
+            }
+            if (lane == 0) {
+                D[j * row + r] = m;
+                split[j * row + r] = static_cast<uint16_t>(m < INFINITY ? arg : j);
+            }
+        }
+        __syncthreads();
+    }
+}
+
 // The last level (row b only, entry +1) and the backtrack, one workgroup. The path's rows
 // at the checkpoint levels come from jump, one dependent read per kDpCheck levels;
 // then one lane per stretch between checkpoints walks its split entries, and the entries
@@ -1134,14 +1178,8 @@ __global__ __launch_bounds__(1024) void k_dp_last(int32_t nbins, int32_t k, void
         *status = hdr[2];
         return;
     }
-    if (hdr[5]) {   // a wait of k_dp_run ran out
-        for (int j = tid; j < k; j += 1024) codebook[j] = -1.0 + 2.0 * j / (k - 1);
-        if (tid == 0) {
-            *cost = INFINITY;
-            *status = 2;
-        }
-        return;
-    }
+    const bool alone = hdr[5] != 0;   // a wait of k_dp_run ran out
+    if (alone) dp_levels_alone(nbins, k, b, keff, ws);
     const double* Dp = at<double>(ws, L.d) + (keff - 1) * row;
     const double zr0 = Z0[b], zr1 = Z1[b], zr2 = Z2[b];
     double best = INFINITY;
@@ -1180,9 +1218,16 @@ __global__ __launch_bounds__(1024) void k_dp_last(int32_t nbins, int32_t k, void
         node[keff - 1] = a - 1;
         // checkpoint levels below keff - 1, multiples of kDpCheck
         int x = a - 1;
-        for (int st = (keff - 2) / kDpCheck; st >= 1; --st) {
-            x = at<uint16_t>(ws, L.jump)[static_cast<size_t>(st) * row + x];
-            node[st * kDpCheck] = x;
+        if (alone) {   // without jump
+            for (int j = keff - 1; j > 1; --j) {
+                x = at<uint16_t>(ws, L.split)[static_cast<size_t>(j) * row + x] - 1;
+                node[j - 1] = x;
+            }
+        } else {
+            for (int st = (keff - 2) / kDpCheck; st >= 1; --st) {
+                x = at<uint16_t>(ws, L.jump)[static_cast<size_t>(st) * row + x];
+                node[st * kDpCheck] = x;
+            }
         }
         node[0] = 0;
     }
@@ -1313,7 +1358,7 @@ hipError_t launch_histogram(const Tile* tiles, int64_t n_tiles, const int32_t* t
 
 hipError_t launch_dp(const uint64_t* hist, int32_t nbins, int32_t k, void* ws,
                      double* codebook_out, double* cost_out, int32_t* status_out,
-                     hipStream_t stream)
+                     hipStream_t stream, int32_t polls)
 {
     hipLaunchKernelGGL(k_dp_prep, dim3(1 + (k > kDpEntry ? kDpFill : 0)), dim3(kThreads), 0, stream,
                        hist, nbins, k, ws);
@@ -1325,7 +1370,7 @@ hipError_t launch_dp(const uint64_t* hist, int32_t nbins, int32_t k, void* ws,
     }
     if (k > kDpEntry)
         hipLaunchKernelGGL(k_dp_run, dim3((nbins + kDpTile - 1) / kDpTile), dim3(kDpRunThreads), 0,
-                           stream, nbins, k, ws);
+                           stream, nbins, k, polls, ws);
     if (k - 2 >= kDpCheck)
         hipLaunchKernelGGL(k_dp_jump, dim3(nbins / 256 + 1, (k - 2) / kDpCheck), dim3(256), 0,
                            stream, nbins, k, ws);

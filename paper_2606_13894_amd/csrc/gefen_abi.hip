@@ -846,8 +846,10 @@ int gefen_histogram(gefen_state* st, const gefen_tensor* grads, int32_t n_tensor
     return run_histogram(st, hist_out, stream);
 }
 
-int gefen_dp_codebook(const uint64_t* hist, int32_t nbins, int32_t k, double* codebook_out,
-                      double* cost_out, int32_t* status_out, void* stream_)
+// gefen_dp_codebook with the DP's `polls` given; exported for the tests, not part of the ABI.
+int gefen_internal_dp_codebook(const uint64_t* hist, int32_t nbins, int32_t k,
+                               double* codebook_out, double* cost_out, int32_t* status_out,
+                               int32_t polls, void* stream_)
 {
     g_err.clear();
     if (!hist || !codebook_out || !cost_out || !status_out)
@@ -857,10 +859,18 @@ int gefen_dp_codebook(const uint64_t* hist, int32_t nbins, int32_t k, double* co
     hipStream_t stream = as_stream(stream_);
     void* ws = nullptr;
     GEFEN_HIP(hipMallocAsync(&ws, dp_workspace_bytes(nbins, k), stream));
-    hipError_t e = launch_dp(hist, nbins, k, ws, codebook_out, cost_out, status_out, stream);
+    hipError_t e =
+        launch_dp(hist, nbins, k, ws, codebook_out, cost_out, status_out, stream, polls);
     (void)hipFreeAsync(ws, stream);
     if (e != hipSuccess) return fail(GEFEN_EHIP, "DP launch failed: %s", hipGetErrorString(e));
     return GEFEN_OK;
+}
+
+int gefen_dp_codebook(const uint64_t* hist, int32_t nbins, int32_t k, double* codebook_out,
+                      double* cost_out, int32_t* status_out, void* stream)
+{
+    return gefen_internal_dp_codebook(hist, nbins, k, codebook_out, cost_out, status_out,
+                                      kDpPolls, stream);
 }
 
 int gefen_dp_codebook_static(const uint64_t* hist, int32_t nbins, int32_t k, double* codebook_out,

@@ -129,11 +129,13 @@ hipError_t launch_histogram(const Tile* tiles, int64_t n_tiles, const int32_t* t
                             const HTile* htiles, const float* am_partials, const Seg* segs,
                             int32_t nbins, uint64_t* hist, int32_t ways, hipStream_t stream);
 
-// DP over a device histogram. ws must hold dp_workspace_bytes(nbins, k) bytes.
+// DP over a device histogram. ws must hold dp_workspace_bytes(nbins, k) bytes. `polls`: of
+// one wait between its row tiles, at most (a test passes -1: every tile gives up).
+constexpr int32_t kDpPolls = 1 << 20;
 size_t dp_workspace_bytes(int32_t nbins, int32_t k);
 hipError_t launch_dp(const uint64_t* hist, int32_t nbins, int32_t k, void* ws,
                      double* codebook_out, double* cost_out, int32_t* status_out,
-                     hipStream_t stream);
+                     hipStream_t stream, int32_t polls = kDpPolls);
 
 // Install a float64 codebook into a slot: fp32 entries, fp64 copy, midpoints, guide.
 hipError_t launch_install_codebook(const double* cb64_in, int32_t k, int32_t ng,

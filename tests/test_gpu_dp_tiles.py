@@ -1,7 +1,9 @@
 """The DP's levels in one launch (gefen_dp_codebook) against the oracle's full scan, bit for
 bit: bins and entries around the 16-row tiles and the first level of that launch, tiles that
-a level reaches late, windows longer than a chunk with and without pruning, and two DPs at
-once on two streams."""
+a level reaches late, windows longer than a chunk with and without pruning, two DPs at
+once on two streams, and waits between the tiles that run out."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -48,3 +50,24 @@ def test_two_streams():
             ref = oracle.dp_codebook(h, 256)
             assert status == ref[3] and cost == ref[1]
             np.testing.assert_array_equal(cb.cpu().numpy(), ref[0])
+
+
+@pytest.mark.parametrize("nbins,k", [(40, 9), (200, 50), (1000, 34), (1024, 256)])
+@pytest.mark.parametrize("kind", ["bell", "gaps"])
+def test_waits_that_run_out(nbins, k, kind):
+    """Every wait between the row tiles given up at once (a poll limit below none): one
+    workgroup takes the levels instead, with the same result."""
+    h = histogram(kind, nbins, seed=nbins + k)
+    d = torch.from_numpy(h.view(np.int64).copy()).cuda()
+    cb = torch.empty(k, dtype=torch.float64, device="cuda")
+    cost = torch.empty(1, dtype=torch.float64, device="cuda")
+    status = torch.empty(1, dtype=torch.int32, device="cuda")
+    call = gf.load_library().gefen_internal_dp_codebook
+    p = ctypes.c_void_p
+    assert call(p(d.data_ptr()), ctypes.c_int32(nbins), ctypes.c_int32(k), p(cb.data_ptr()),
+                p(cost.data_ptr()), p(status.data_ptr()), ctypes.c_int32(-1),
+                p(torch.cuda.current_stream().cuda_stream)) == 0
+    ref = oracle.dp_codebook(h, k)
+    assert status.item() == ref[3]
+    np.testing.assert_array_equal(cb.cpu().numpy(), ref[0])
+    assert cost.item() == ref[1]
