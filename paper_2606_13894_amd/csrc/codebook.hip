@@ -441,6 +441,20 @@ __device__ __forceinline__ double dp_cost_free(double zr0, double zr1, double zr
     return S2 - S1 * S1 / S0;
 }
 
+// At most dp_cost_free's value (or not a number), without its division: the quotient from a
+// float32 reciprocal, raised by 2^-20 (its error is below 2^-22), so that the rounded
+// difference is no larger; an S0 of 0 gives minus infinity or NaN. A candidate whose value
+// from this one is above the minimum so far is none, and a whole window mostly is.
+__device__ __forceinline__ double dp_cost_below(double zr0, double zr1, double zr2, double z0,
+                                                double z1, double z2)
+{
+    const double S0 = zr0 - z0;
+    const double S1 = zr1 - z1;
+    const double S2 = zr2 - z2;
+    const double inv = static_cast<double>(__builtin_amdgcn_rcpf(static_cast<float>(S0)));
+    return S2 - S1 * S1 * inv * (1.0 + 0x1p-20);
+}
+
 __device__ __forceinline__ double dp_cost_forced(double a, double zr0, double zr1, double zr2,
                                                  double z0, double z1, double z2)
 {
@@ -643,6 +657,12 @@ __device__ __forceinline__ double wave_min(double v)
 //
 // Values and argmins are those of the full scan, bit for bit.
 //
+// Where rows may not be pruned (counts times bins of 2^50 or more: histograms accumulated
+// over many steps) every row takes its whole window, 2.1e9 candidates at 4096 bins and 256
+// entries, here and in k_dp_run; dp_cost_below spares most of them the division, and the
+// windows are read once. The whole DP then takes 3.4 ms (17.1 ms with the windows taken chunk
+// by chunk twice as below, 4.7 ms for the full scan of a launch a level).
+//
 // The candidates fall from 1.9e9 to 5e7 at b = 4096, k = 256, and a level is bound by its
 // launch and two dependent trips to memory, at the first levels by long windows too: the
 // first 64 candidates are loaded before the header and the lower bound are known (loading
@@ -688,7 +708,32 @@ __global__ __launch_bounds__(kDpThreads) void k_dp_level(int32_t nbins, int32_t 
             arg = r - lane;
         }
     }
-    for (int l = r - 64 - lane; l >= lo; l -= 64) {   // falling l: the last minimum kept
+    if (!prune) {   // whole windows, the loads of four chunks in flight
+        constexpr int kAhead = 4;
+        for (int l0 = r - 64 - lane; l0 >= lo; l0 -= 64 * kAhead) {
+            double y0[kAhead], y1[kAhead], y2[kAhead], y[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                const int x = l0 - 64 * u >= lo ? l0 - 64 * u - 1 : lo - 1;
+                y0[u] = Z0[x];
+                y1[u] = Z1[x];
+                y2[u] = Z2[x];
+                y[u] = Dp[x];
+            }
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                const int l = l0 - 64 * u;
+                if (l < lo || y[u] + dp_cost_below(zr0, zr1, zr2, y0[u], y1[u], y2[u]) > best)
+                    continue;
+                const double c = y[u] + dp_cost_free(zr0, zr1, zr2, y0[u], y1[u], y2[u]);
+                if (c <= best && c < INFINITY) {
+                    best = c;
+                    arg = l;
+                }
+            }
+        }
+    }
+    for (int l = r - 64 - lane; prune && l >= lo; l -= 64) {   // falling l: the last minimum kept
         const double c = Dp[l - 1] + dp_cost_free(zr0, zr1, zr2, Z0[l - 1], Z1[l - 1], Z2[l - 1]);
         if (c <= best && c < INFINITY) {
             best = c;
@@ -715,7 +760,7 @@ __global__ __launch_bounds__(kDpThreads) void k_dp_level(int32_t nbins, int32_t 
         bestl = a;
         // the smallest l within slack, from the lower bound up (bestl ends the search)
         from = lo;
-        for (int base = lo;; base += 64) {
+        for (int base = lo; prune; base += 64) {
             const int l = base + lane;
             bool ok = false;
             if (l <= r) {
@@ -826,6 +871,7 @@ __global__ __launch_bounds__(kDpRunThreads) void k_dp_run(int32_t nbins, int32_t
     __shared__ double zs[3][kMaxBins + 1];
     __shared__ double ds[kMaxBins + 1];
     __shared__ double cand[kDpChunk * kDpPitch];
+    __shared__ uint16_t carg[kDpChunk * kDpPitch];   // whole windows: the candidates' l
     __shared__ double wmin[8], whigh[8];   // the scan's minima, by wave: all, and above the chunk
     __shared__ int lo[kDpTile];
     // by level parity: largest window and smallest lower bound of the level's rows, smallest
@@ -888,6 +934,10 @@ __global__ __launch_bounds__(kDpRunThreads) void k_dp_run(int32_t nbins, int32_t
     const int q = tid % kDpTile, slot = tid / kDpTile;   // candidates: this lane's row
     const int cq = tid >> 4, sub = tid & 15;             // minima: this lane's row
     const bool minima = tid < 16 * kDpTile;
+    const double slack_all = 1.1102230246251565e-16 * 256.0 * total;
+    const double slack_own =
+        minima && R0 + cq <= top
+            ? 1.1102230246251565e-16 * 256.0 * at<double>(ws, L.z0)[R0 + cq] : 0.0;
     unsigned long long ahead = kDpUnset;
     for (int j = j0; j < keff; ++j) {
         const int rmax = lift + j;
@@ -931,9 +981,7 @@ __global__ __launch_bounds__(kDpRunThreads) void k_dp_run(int32_t nbins, int32_t
         int hi = 0x7fffffff;   // no row needs a candidate above
         const double zr0 = zs[0][r], zr1 = zs[1][r], zr2 = zs[2][r];
         const double slack1 = 1.1102230246251565e-16 * 32.0 * static_cast<double>(k);
-        // of the level's last row with the total count (k_dp_level)
-        const double slack0 =
-            minima ? 1.1102230246251565e-16 * 256.0 * (cr < rmax ? zs[0][cr] : total) : 0.0;
+        const double slack0 = cr < rmax ? slack_own : slack_all;   // as in k_dp_level
         auto candidates = [&](int c0) {
             const int l = lq + c0 + slot;
             double c = INFINITY;
@@ -977,7 +1025,37 @@ __global__ __launch_bounds__(kDpRunThreads) void k_dp_run(int32_t nbins, int32_t
                 in = f < in ? f : in;
             }
         };
-        bool done = false;
+        bool done = !prune;
+        if (!prune) {   // whole windows: a lane's minimum over every kDpChunk-th candidate
+            double best = INFINITY;
+            int arg = j;
+            if (lq < 0x7fffffff) {
+                for (int l = r - slot; l >= j; l -= kDpChunk) {   // falling l: the last one kept
+                    const double y = ds[l - 1], y0 = zs[0][l - 1], y1 = zs[1][l - 1],
+                                 y2 = zs[2][l - 1];
+                    if (y + dp_cost_below(zr0, zr1, zr2, y0, y1, y2) > best) continue;
+                    const double c = y + dp_cost_free(zr0, zr1, zr2, y0, y1, y2);
+                    if (c <= best && c < INFINITY) {
+                        best = c;
+                        arg = l;
+                    }
+                }
+            }
+            cand[slot * kDpPitch + q] = best;
+            carg[slot * kDpPitch + q] = static_cast<uint16_t>(arg);
+            lds_barrier();
+            if (minima) {
+                for (int u = 0; u < kDpEach; ++u) m = fmin(m, cand[(u * 16 + sub) * kDpPitch + cq]);
+                m = row_min(m);
+                for (int u = 0; u < kDpEach; ++u) {
+                    const int x = (u * 16 + sub) * kDpPitch + cq;
+                    const int f = carg[x] - lc;
+                    if (cand[x] == m && f < ib) ib = f;
+                }
+                ib = row_imin(ib);
+                in = 0;
+            }
+        }
         if (prune && W > kDpChunk) {
             const int rt = top < rmax ? top : rmax, lt = lo[rt - R0];
             const int g = llow + kDpChunk / 2 - 1;
@@ -1007,7 +1085,7 @@ __global__ __launch_bounds__(kDpRunThreads) void k_dp_run(int32_t nbins, int32_t
             const double mt = row_min(wmin[lane & 7]);
             const double mh = row_min(whigh[lane & 7]);
             const double neart =
-                mt + (1.1102230246251565e-16 * 256.0 * (rt < rmax ? t0 : total) + slack1 * mt);
+                mt + ((rt < rmax ? 1.1102230246251565e-16 * 256.0 * t0 : slack_all) + slack1 * mt);
             if (mh > neart) {
                 if (minima) reduce(0, kDpEach / 2, true, true);
                 done = true;

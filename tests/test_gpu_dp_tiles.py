@@ -35,6 +35,16 @@ def test_long_windows_without_pruning():
     _check(h, 11)
 
 
+@pytest.mark.parametrize("kind", ["bell", "flat", "comb", "gaps"])
+@pytest.mark.parametrize("nbins,k", [(48, 9), (500, 64), (2000, 40), (4096, 256)])
+def test_whole_windows(nbins, k, kind):
+    """Counts too large to prune: every candidate of every row, ties included."""
+    h = histogram(kind, nbins, seed=nbins + k)
+    h *= np.uint64(int(2.0 ** 51 / nbins / float(h.sum())) + 1)
+    assert float(h.sum()) * nbins > 2.0 ** 50
+    _check(h, k)
+
+
 def test_two_streams():
     hs = [histogram(kind, 4096, seed=9) for kind in ("bell", "two_scales")]
     dev = [torch.from_numpy(h.view(np.int64).copy()).cuda() for h in hs]
