@@ -86,6 +86,9 @@ typedef struct gefen_state gefen_state;   /* opaque, library-owned */
  *                  paper leaves it open -- the optimizer eps, 1e-8, is the default).
  *  stream          stream for all work; synchronised once (the inferred periods
  *                  size the state).
+ * Inference takes device memory of its own and frees it before the state's is
+ * allocated: 64 MiB and half a byte per element at most for its sums, and up to as much
+ * again for sizes of hundreds of divisors (about 0.1 bytes per element for weights).
  *  out             receives the new state.
  * Errors: EINVAL, EDTYPE, EHIP, ENOMEM. A degenerate codebook fit returns OK (the
  * fallback codebook is installed); query it with gefen_get_fit_info.
@@ -157,7 +160,8 @@ int gefen_fit_codebook(gefen_state* st, const gefen_tensor* grads, int32_t n_ten
 /* gefen_partition_scores -- Alg. 2 on one tensor: the divisors of numel in
  * increasing order, the score S(p) of each (partition-score equation; S(numel) = 0),
  * and the chosen period. divisors_out/scores_out are host arrays of `cap` entries;
- * *n_div receives the divisor count (EINVAL if it exceeds cap). Synchronises. */
+ * *n_div receives the divisor count (EINVAL if it exceeds cap). Synchronises. Its device
+ * memory is gefen_init's for inference. */
 int gefen_partition_scores(const gefen_tensor* grad, double eps_part, int64_t* divisors_out,
                            double* scores_out, int32_t cap, int32_t* n_div,
                            int64_t* period_out, void* stream);

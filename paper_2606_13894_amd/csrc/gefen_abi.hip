@@ -336,18 +336,19 @@ int plan_tiles(gefen_state* st, const std::vector<std::vector<int64_t>>& starts)
 }
 
 // Alg. 2 for a list of tensors. Writes one period per tensor (host), and optionally the
-// divisors and their scores (host, concatenated in tensor order). Tables, sums and results
-// share one device allocation.
+// divisors and their scores (host, concatenated in tensor order). Tables, results, and the
+// sums and contrasts, which the plans use one after another, share one device allocation.
 int infer_periods(const std::vector<gefen_tensor>& ts, double eps, hipStream_t stream,
                   std::vector<int64_t>& periods, std::vector<int64_t>* divs_out,
                   std::vector<double>* scores_out)
 {
-    PartPlan plan;
+    std::vector<PartInput> in;
     int64_t total = 0;
-    for (const gefen_tensor& g : ts) total += g.numel;
-    for (const gefen_tensor& g : ts) part_add(plan, g.ptr, g.numel, g.dtype, total);
-    part_finish(plan);
-    const size_t ns = plan.scores.size(), nt = ts.size();
+    for (const gefen_tensor& g : ts) {
+        in.push_back(PartInput{g.ptr, g.numel, g.dtype});
+        total += g.numel;
+    }
+    const std::vector<PartPlan> plans = part_plans(in, part_budget(total));
     size_t bytes = 0;
     auto room = [&](size_t b) {
         const size_t at = bytes;
@@ -355,55 +356,64 @@ int infer_periods(const std::vector<gefen_tensor>& ts, double eps, hipStream_t s
         return at;
     };
     // the tables, copied from one host image
-    size_t n_jobs = 0;
-    for (const auto& l : plan.launches) n_jobs += l.size();
-    const size_t o_tensors = room(sizeof(PartTensor) * nt);
-    const size_t o_units = room(sizeof(PartUnit) * plan.units.size());
-    const size_t o_phase = room(sizeof(int32_t) * plan.phase_end.size());
-    const size_t o_keep = room(sizeof(int64_t) * plan.keep.size());
-    const size_t o_jobs = room(sizeof(PartJob) * n_jobs);
-    const size_t o_scores = room(sizeof(PartScore) * ns);
-    const size_t o_first = room(sizeof(int32_t) * nt);
-    const size_t o_count = room(sizeof(int32_t) * nt);
-    std::vector<char> image(bytes);
-    std::memcpy(&image[o_tensors], plan.tensors.data(), sizeof(PartTensor) * nt);
-    std::memcpy(image.data() + o_units, plan.units.data(), sizeof(PartUnit) * plan.units.size());
-    std::memcpy(image.data() + o_phase, plan.phase_end.data(),
-                sizeof(int32_t) * plan.phase_end.size());
-    std::memcpy(image.data() + o_keep, plan.keep.data(), sizeof(int64_t) * plan.keep.size());
-    size_t at = o_jobs;
-    for (const auto& l : plan.launches) {
-        std::memcpy(image.data() + at, l.data(), sizeof(PartJob) * l.size());
-        at += sizeof(PartJob) * l.size();
+    std::vector<char> image;
+    auto table = [&](const auto& v) {
+        const size_t size = sizeof(v[0]) * v.size(), at = room(size);
+        image.resize(bytes);
+        if (size) std::memcpy(image.data() + at, v.data(), size);
+        return at;
+    };
+    struct Tables {
+        size_t tensors, units, phase, keep, spans, direct, store, jobs, scores, first, count;
+    };
+    std::vector<Tables> tables;
+    size_t nt = 0, ns = 0, sums = 0, parts = 0;
+    for (const PartPlan& p : plans) {
+        std::vector<PartJob> jobs;
+        for (const auto& l : p.launches) jobs.insert(jobs.end(), l.begin(), l.end());
+        tables.push_back(Tables{table(p.tensors), table(p.units), table(p.phase_end),
+                                table(p.keep), table(p.spans), table(p.direct), table(p.store),
+                                table(jobs), table(p.scores), table(p.first), table(p.count)});
+        nt += p.tensors.size();
+        ns += p.scores.size();
+        sums = std::max(sums, static_cast<size_t>(p.sums));
+        parts = std::max(parts, static_cast<size_t>(p.parts));
     }
-    std::memcpy(&image[o_scores], plan.scores.data(), sizeof(PartScore) * ns);
-    std::memcpy(&image[o_first], plan.first.data(), sizeof(int32_t) * nt);
-    std::memcpy(&image[o_count], plan.count.data(), sizeof(int32_t) * nt);
     // results, then sums and partial contrasts
     const size_t o_periods = room(sizeof(int64_t) * nt);
     const size_t o_values = room(sizeof(double) * ns);
     const size_t results = bytes - o_periods;
-    const size_t o_sums = room(sizeof(double) * static_cast<size_t>(plan.sums));
-    const size_t o_part = room(sizeof(double) * static_cast<size_t>(plan.parts));
+    const size_t o_sums = room(sizeof(double) * sums);
+    const size_t o_part = room(sizeof(double) * parts);
+    std::vector<char> host(results);
     char* dev = nullptr;
     GEFEN_HIP(hipMalloc(reinterpret_cast<void**>(&dev), bytes));
-    std::vector<char> host(results);
     auto run = [&]() -> int {
         GEFEN_HIP(hipMemcpyAsync(dev, image.data(), image.size(), hipMemcpyHostToDevice, stream));
-        PartDevice d{};
-        d.tensors = reinterpret_cast<PartTensor*>(dev + o_tensors);
-        d.units = reinterpret_cast<PartUnit*>(dev + o_units);
-        d.phase_end = reinterpret_cast<int32_t*>(dev + o_phase);
-        d.keep = reinterpret_cast<int64_t*>(dev + o_keep);
-        d.jobs = reinterpret_cast<PartJob*>(dev + o_jobs);
-        d.scores = reinterpret_cast<PartScore*>(dev + o_scores);
-        d.first = reinterpret_cast<int32_t*>(dev + o_first);
-        d.count = reinterpret_cast<int32_t*>(dev + o_count);
-        d.periods = reinterpret_cast<int64_t*>(dev + o_periods);
-        d.values = reinterpret_cast<double*>(dev + o_values);
-        d.sums = reinterpret_cast<double*>(dev + o_sums);
-        d.part = reinterpret_cast<double*>(dev + o_part);
-        GEFEN_HIP(launch_partition(plan, d, eps, stream));
+        int64_t* period = reinterpret_cast<int64_t*>(dev + o_periods);
+        double* value = reinterpret_cast<double*>(dev + o_values);
+        for (size_t i = 0; i < plans.size(); ++i) {
+            const Tables& o = tables[i];
+            PartDevice d{};
+            d.tensors = reinterpret_cast<PartTensor*>(dev + o.tensors);
+            d.units = reinterpret_cast<PartUnit*>(dev + o.units);
+            d.phase_end = reinterpret_cast<int32_t*>(dev + o.phase);
+            d.keep = reinterpret_cast<int64_t*>(dev + o.keep);
+            d.spans = reinterpret_cast<PartSpan*>(dev + o.spans);
+            d.direct = reinterpret_cast<int32_t*>(dev + o.direct);
+            d.store = reinterpret_cast<int64_t*>(dev + o.store);
+            d.jobs = reinterpret_cast<PartJob*>(dev + o.jobs);
+            d.scores = reinterpret_cast<PartScore*>(dev + o.scores);
+            d.first = reinterpret_cast<int32_t*>(dev + o.first);
+            d.count = reinterpret_cast<int32_t*>(dev + o.count);
+            d.periods = period;
+            d.values = value;
+            d.sums = reinterpret_cast<double*>(dev + o_sums);
+            d.part = reinterpret_cast<double*>(dev + o_part);
+            GEFEN_HIP(launch_partition(plans[i], d, eps, stream));
+            period += plans[i].tensors.size();
+            value += plans[i].scores.size();
+        }
         GEFEN_HIP(hipMemcpyAsync(host.data(), dev + o_periods, results, hipMemcpyDeviceToHost,
                                  stream));
         GEFEN_HIP(hipStreamSynchronize(stream));
@@ -421,7 +431,8 @@ int infer_periods(const std::vector<gefen_tensor>& ts, double eps, hipStream_t s
     }
     if (divs_out) {
         divs_out->clear();
-        for (const PartScore& s : plan.scores) divs_out->push_back(s.p);
+        for (const PartPlan& p : plans)
+            for (const PartScore& s : p.scores) divs_out->push_back(s.p);
     }
     return GEFEN_OK;
 }

@@ -153,6 +153,9 @@ struct PartDevice {
     const PartUnit* units;
     const int32_t* phase_end;
     const int64_t* keep;
+    const PartSpan* spans;
+    const int32_t* direct;
+    const int64_t* store;
     const PartJob* jobs;          // the launches' jobs one after another
     const PartScore* scores;
     const int32_t *first, *count;

@@ -215,6 +215,63 @@ __global__ __launch_bounds__(kPartThreads) void k_part_base(const PartTensor* __
     }
 }
 
+// The direct divisors: z of a span and two blocks beyond it in LDS, one logarithm an element
+// for all of them, then a wave a divisor at a time: g lanes a block, 64 / g blocks, each
+// contrasted with the next one's lanes. Bound by the logarithms: 262M bfloat16 gradients and
+// one divisor 0.94 ms.
+__global__ __launch_bounds__(kPartDirectThreads) void k_part_direct(
+    const PartSpan* __restrict__ spans, int32_t n_spans, const int32_t* __restrict__ direct,
+    const int64_t* __restrict__ store, const PartTensor* __restrict__ tensors, double eps,
+    double* __restrict__ sums, double* __restrict__ part)
+{
+    extern __shared__ double S[];
+    const int64_t item = blockIdx.x;
+    const PartSpan sp =
+        spans[find_item(spans, n_spans, item, [](const PartSpan& x) { return x.item0; })];
+    const PartTensor t = tensors[sp.tensor];
+    const int64_t it = item - sp.item0;
+    const int64_t e0 = it * kPartSpan;
+    const int64_t e1 = e0 + kPartSpan < t.n ? e0 + kPartSpan : t.n;
+    const int64_t stop = e1 + 2 * direct[sp.first + sp.count - 1];
+    const int len = static_cast<int>((stop < t.n ? stop : t.n) - e0);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+#pragma unroll 4
+    for (int i = tid; i < len; i += kPartDirectThreads) S[i] = z_at(t.grad, t.gdtype, e0 + i, eps);
+    __syncthreads();
+    for (int d = wave; d < sp.count; d += kPartDirectThreads / 64) {
+        const int p = direct[sp.first + d];
+        const int64_t first = (e0 + p - 1) / p, nb = t.n / p;
+        const int64_t next_first = (e1 + p - 1) / p;
+        // contrasts of first .. last - 1; block `last` is read
+        const int64_t last = next_first < nb - 1 ? next_first : nb - 1;
+        const int cnt = static_cast<int>(last - first);
+        const int64_t at = store[sp.store0 + d];
+        double* __restrict__ o = at < 0 ? nullptr : sums + at + first;
+        const int own = static_cast<int>(next_first - first);   // sums of this item
+        const double* __restrict__ s = S + (first * p - e0);
+        const int gl = p <= 32 ? 0 : p <= 256 ? 2 : 4;
+        const int g = 1 << gl, per = 64 >> gl, sub = lane & (g - 1), blk = lane >> gl;
+        double acc = 0.0;
+        for (int b = 0; b < cnt || b < own; b += per - 1) {
+            const int i = b + blk;
+            double v = 0.0;
+            if (i <= cnt) {
+#pragma unroll 4
+                for (int k = sub; k < p; k += g) v += s[i * p + k];
+            }
+            for (int off = 1; off < g; off <<= 1) v += __shfl_xor(v, off);
+            const double next = __shfl(v, (lane + g) & 63);
+            if (sub == 0 && blk + 1 < per) {
+                if (i < cnt) acc += fabs(next - v);
+                if (o && i < own) o[i] = v;
+            }
+        }
+        acc = wave_sum63(acc);
+        if (lane == 63) part[sp.out + d * sp.n_items + it] = acc;
+    }
+}
+
 // Terms [a, b) of a job's source, summed by `stride` threads of which this is `tid`.
 __device__ __forceinline__ double term_sum(const PartJob& j, const PartTensor& t,
                                            const double* __restrict__ sums, double eps, int64_t a,
@@ -339,10 +396,16 @@ hipError_t launch_partition(const PartPlan& plan, const PartDevice& d, double ep
 {
     const int32_t nt = static_cast<int32_t>(plan.tensors.size());
     const int32_t ns = static_cast<int32_t>(plan.scores.size());
-    if (plan.groups > 0x7fffffffLL) return hipErrorInvalidValue;
+    if (plan.groups > 0x7fffffffLL || plan.span_items > 0x7fffffffLL) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_part_base, dim3(static_cast<unsigned>(plan.groups)), dim3(kPartThreads),
                        sizeof(double) * plan.lds_doubles, stream, d.tensors, nt, d.units,
                        d.phase_end, d.keep, eps, d.sums, d.part);
+    if (plan.span_items)
+        hipLaunchKernelGGL(k_part_direct, dim3(static_cast<unsigned>(plan.span_items)),
+                           dim3(kPartDirectThreads),
+                           sizeof(double) * (kPartSpan + 2 * plan.direct_max), stream, d.spans,
+                           static_cast<int32_t>(plan.spans.size()), d.direct, d.store, d.tensors,
+                           eps, d.sums, d.part);
     const PartJob* jobs = d.jobs;
     for (const std::vector<PartJob>& l : plan.launches) {
         if (l.empty()) continue;

@@ -1,6 +1,7 @@
 // Runs the plan of block inference (part_plan.h) on the CPU, term by term as the kernels
 // index it, and compares every score with the definition (z evaluated once per divisor).
-// Usage: part_plan_check n [n ...]   -- one plan over tensors of these sizes.
+// Usage: part_plan_check n [n ...]   -- one plan over tensors of these sizes; with PART_BUDGET
+// the plans that store at most so many bytes at a time.
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -10,23 +11,9 @@
 
 using namespace gefen;
 
-int main(int argc, char** argv)
+// Plan P over tensors whose z are `z`.
+int check(const PartPlan& P, const std::vector<std::vector<double>>& z)
 {
-    // PART_SCALE: as if the plan held that many times the elements (longer runs)
-    const int64_t scale = std::getenv("PART_SCALE") ? std::atoll(std::getenv("PART_SCALE")) : 1;
-    PartPlan P;
-    std::vector<std::vector<double>> z;   // z of every tensor
-    std::mt19937_64 gen(17);
-    int64_t total = 0;
-    for (int a = 1; a < argc; ++a) total += std::atoll(argv[a]);
-    for (int a = 1; a < argc; ++a) {
-        const int64_t n = std::atoll(argv[a]);
-        z.emplace_back(n);
-        std::normal_distribution<double> d(0.0, 1.0);
-        for (double& v : z.back()) v = std::log(std::pow(d(gen), 2) + 1e-8);
-        part_add(P, nullptr, n, 0, total * scale);
-    }
-    part_finish(P);
     const double unset = std::nan("");
     std::vector<double> sums(P.sums, unset), part(P.parts, unset);
     int64_t written = 0;
@@ -92,6 +79,34 @@ int main(int argc, char** argv)
         }
     }
     if (groups != P.groups) return std::puts("group count"), 1;
+    int64_t span_items = 0;   // the direct divisors
+    for (const PartSpan& sp : P.spans) {
+        const int64_t n = P.tensors.at(sp.tensor).n;
+        if (sp.item0 != span_items || sp.count < 1) return std::puts("span items"), 1;
+        span_items += sp.n_items;
+        for (int64_t it = 0; it < sp.n_items; ++it) {
+            const int64_t e0 = it * kPartSpan, e1 = std::min(e0 + kPartSpan, n);
+            const int64_t top = P.direct.at(sp.first + sp.count - 1);
+            if (top > P.direct_max || top > kPartDirectMax) return std::puts("direct divisor"), 1;
+            const int64_t end = std::min(e1 + 2 * top, n);   // elements in LDS
+            for (int64_t d = 0; d < sp.count; ++d) {
+                const int64_t p = P.direct.at(sp.first + d), nb = n / p;
+                const int64_t first = (e0 + p - 1) / p, last = std::min((e1 + p - 1) / p, nb - 1);
+                const int64_t at = P.store.at(sp.store0 + d), own = (e1 + p - 1) / p;
+                double acc = 0.0, prev = 0.0;
+                for (int64_t i = first; i <= last || i < own; ++i) {
+                    if (i * p < e0 || (i + 1) * p > end) return std::puts("block outside the span"), 1;
+                    double s = 0.0;
+                    for (int64_t k = i * p; k < (i + 1) * p; ++k) s += z[sp.tensor].at(k);
+                    if (i > first && i <= last) acc += std::fabs(s - prev);
+                    prev = s;
+                    if (at >= 0 && i < own) put(sums, at + i, s);
+                }
+                put(part, sp.out + d * sp.n_items + it, acc);
+            }
+        }
+    }
+    if (span_items != P.span_items) return std::puts("span count"), 1;
     for (const auto& l : P.launches) {
         int64_t items = 0;
         std::vector<std::pair<int64_t, double>> out;   // a launch reads nothing it writes
@@ -151,4 +166,44 @@ int main(int argc, char** argv)
     }
     std::printf("largest relative difference %.3g\n", worst);
     return worst < 1e-9 ? 0 : 1;
+}
+
+int main(int argc, char** argv)
+{
+    // PART_SCALE: as if the plan held that many times the elements (longer runs)
+    const int64_t scale = std::getenv("PART_SCALE") ? std::atoll(std::getenv("PART_SCALE")) : 1;
+    const char* limit = std::getenv("PART_BUDGET");
+    std::vector<std::vector<double>> z;   // z of every tensor
+    std::vector<PartInput> in;
+    std::mt19937_64 gen(17);
+    int64_t total = 0;
+    for (int a = 1; a < argc; ++a) {
+        const int64_t n = std::atoll(argv[a]);
+        z.emplace_back(n);
+        std::normal_distribution<double> d(0.0, 1.0);
+        for (double& v : z.back()) v = std::log(std::pow(d(gen), 2) + 1e-8);
+        in.push_back(PartInput{nullptr, n, 0});
+        total += n;
+    }
+    if (!limit) {
+        PartPlan P;
+        for (const PartInput& t : in) part_add(P, nullptr, t.n, 0, total * scale, part_budget(total * scale));
+        part_finish(P);
+        return check(P, z);
+    }
+    const int64_t budget = std::atoll(limit);
+    size_t at = 0;
+    for (const PartPlan& P : part_plans(in, budget)) {
+        const size_t n = P.tensors.size();
+        int64_t least = 0;
+        for (size_t i = 0; i < n; ++i) least = std::max(least, P.shapes.at(P.tensors[i].n).least);
+        std::printf("%zu tensors from %zu: %lld bytes stored, least %lld\n", n, at,
+                    (long long)(8 * P.sums), (long long)least);
+        if (at + n > z.size() || !n) return std::puts("plan's tensors"), 1;
+        if (8 * P.sums > budget && (n > 1 || least < kPartLeastMax))
+            return std::puts("over the budget"), 1;
+        if (check(P, {z.begin() + at, z.begin() + at + n})) return 1;
+        at += n;
+    }
+    return at == z.size() ? 0 : 1;
 }
