@@ -130,7 +130,7 @@ __device__ __forceinline__ void tile_block(const Seg& sg, const Tile& tl, int bi
 // (bfloat16, rows of 2048 and 8192); this takes 148 us and 1.22 ms. Not the flush: storing
 // each workgroup's bins and adding them up in a second kernel instead of the atomics left
 // both kernels' times as they were.
-constexpr int kHistVecs = 8;
+constexpr int kHistVecs = static_cast<int>(kHistVecBlock / 256);
 constexpr int64_t kHistVecGroups = 1024;   // four workgroups a CU
 
 // Elements e .. e + 3 (one vector when `aligned`).
@@ -313,7 +313,7 @@ __global__ __launch_bounds__(kThreads) void k_histogram(const Tile* __restrict__
                                                         const HTile* __restrict__ htiles,
                                                         const float* __restrict__ am_partials,
                                                         const Seg* __restrict__ segs,
-                                                        int32_t nbins,
+                                                        int32_t nbins, int64_t longest,
                                                         uint64_t* __restrict__ hist)
 {
     __shared__ uint32_t h[kMaxBins];
@@ -332,7 +332,7 @@ __global__ __launch_bounds__(kThreads) void k_histogram(const Tile* __restrict__
         const Tile tl = tiles[ti];
         const Seg sg = segs[tl.seg];
         const int kind = tile_kind[ti];
-        if (hist_by_vectors(kind, sg.period) != VEC) continue;
+        if (hist_by_vectors(kind, sg.period, longest) != VEC) continue;
         if constexpr (VEC) {
             if (sg.gdtype == DT_F32)
                 hist_uniform<DT_F32>(sg, tl, half_nb, nbins, h, lane);
@@ -1425,12 +1425,15 @@ hipError_t launch_histogram(const Tile* tiles, int64_t n_tiles, const int32_t* t
     const auto grid = [&](int64_t most) {
         return dim3(static_cast<unsigned>(w < most ? w : most));
     };
+    const int64_t longest = ways & kHistLong ? INT64_MAX : kHistVecBlock;
     if (ways & kHistVec)   // as many workgroups as are resident
         hipLaunchKernelGGL(k_histogram<true>, grid(kHistVecGroups), dim3(kThreads), 0, stream,
-                           tiles, n_tiles, tile_kind, htiles, am_partials, segs, nbins, hist);
+                           tiles, n_tiles, tile_kind, htiles, am_partials, segs, nbins, longest,
+                           hist);
     if (ways & kHistStream)
         hipLaunchKernelGGL(k_histogram<false>, grid(4096), dim3(kThreads), 0, stream, tiles,
-                           n_tiles, tile_kind, htiles, am_partials, segs, nbins, hist);
+                           n_tiles, tile_kind, htiles, am_partials, segs, nbins, longest,
+                           hist);
     return hipGetLastError();
 }
 

@@ -96,7 +96,8 @@ struct gefen_state {
     int64_t* csr = nullptr;
 
     uint64_t* hist = nullptr;
-    std::vector<int32_t> hist_ways;    // per class: the histogram kernels its tiles need
+    std::vector<int32_t> hist_ways;    // per class, and of all tiles: the histogram kernels
+    int32_t hist_ways_all = 0;         // they need
     void* dp_ws = nullptr;
     double* fit_cb64 = nullptr;
     double* fit_cost = nullptr;
@@ -307,14 +308,29 @@ int plan_tiles(gefen_state* st, const std::vector<std::vector<int64_t>>& starts)
     st->n_hblocks = ctx.n_hblocks;
     st->classes = plan.classes;
     st->n_tiles = static_cast<int64_t>(plan.tiles.size());
-    st->hist_ways.assign(plan.classes.size(), 0);
-    for (size_t ci = 0; ci < plan.classes.size(); ++ci)
-        for (int64_t i = 0; i < plan.classes[ci].count; ++i) {
-            const size_t at = static_cast<size_t>(plan.classes[ci].first + i);
-            st->hist_ways[ci] |=
-                hist_by_vectors(plan.kinds[at], st->explicit_blocks ? 0 : st->period[plan.tiles[at].seg])
-                    ? kHistVec : kHistStream;
+    int64_t regs_all = 0, longer_all = 0;
+    bool other_all = false;
+    st->hist_ways.clear();
+    for (const Class& c : plan.classes) {
+        int64_t regs = 0, longer = 0;
+        bool other = false;
+        for (int64_t i = c.first; i < c.first + c.count; ++i) {
+            const Tile& tl = plan.tiles[static_cast<size_t>(i)];
+            const int64_t p = st->explicit_blocks ? 0 : st->period[tl.seg];
+            const int32_t kind = plan.kinds[static_cast<size_t>(i)];
+            if (hist_by_vectors(kind, p, kHistVecBlock))
+                regs += tl.nelem;
+            else if (hist_by_vectors(kind, p, INT64_MAX))
+                longer += tl.nelem;
+            else
+                other = true;
         }
+        st->hist_ways.push_back(hist_ways(regs, longer, other));
+        regs_all += regs;
+        longer_all += longer;
+        other_all = other_all || other;
+    }
+    st->hist_ways_all = hist_ways(regs_all, longer_all, other_all);
     int rc = st->alloc(&st->tiles, sizeof(Tile) * plan.tiles.size(), false);
     if (rc) return rc;
     rc = st->alloc(&st->tile_kind, sizeof(int32_t) * plan.kinds.size(), false);
@@ -451,14 +467,12 @@ CodebookDev codebook_dev(const gefen_state* st)
 // Histogram with the state's blocks into `hist` (already zeroed).
 int run_histogram(gefen_state* st, uint64_t* hist, hipStream_t stream)
 {
-    int32_t ways = 0;
-    for (int32_t w : st->hist_ways) ways |= w;
     for (const Class& c : st->classes)
         if (c.kind == KIND_H)
             GEFEN_HIP(launch_hist_h_absmax(st->tiles + c.first, st->htiles + c.first, c.count,
                                            st->segs, st->h_absmax, stream));
     GEFEN_HIP(launch_histogram(st->tiles, st->n_tiles, st->tile_kind, st->htiles, st->h_absmax,
-                               st->segs, st->nbins, hist, ways, stream));
+                               st->segs, st->nbins, hist, st->hist_ways_all, stream));
     return GEFEN_OK;
 }
 

@@ -66,10 +66,29 @@ struct CodebookDev {
 // infinite a takes zeros instead: finite g gives x = 0, infinite g a NaN, as g / a does.
 // (Three multiply-adds against about a dozen dependent operations of the division.)
 // Tiles whose blocks the histogram kernel takes by 4-element vectors from the block's first
-// element on: uniform blocks of whole vectors that one workgroup's tile holds whole.
-__host__ __device__ __forceinline__ bool hist_by_vectors(int32_t kind, int64_t period)
+// element on: uniform blocks of whole vectors that one workgroup's tile holds whole, of at
+// most `longest` elements: kHistVecBlock, what its registers hold, or any (hist_ways).
+constexpr int64_t kHistVecBlock = 2048;
+__host__ __device__ __forceinline__ bool hist_by_vectors(int32_t kind, int64_t period,
+                                                         int64_t longest)
 {
-    return kind != KIND_H && period > 0 && period % 4 == 0;
+    return kind != KIND_H && period > 0 && period % 4 == 0 && period <= longest;
+}
+
+// The histogram kernels of a launch and whether the vector kernel takes its longer blocks too,
+// for `regs` elements in tiles of hist_by_vectors, `longer` in those of longer blocks and
+// whether there are other tiles. The other kernel, with more waves, is the faster one for the
+// longer blocks (4M elements in rows of 3072, float32: 28 us against 45; 64M: 98 against
+// 122), but beside shorter ones it is one launch more, about 20 us: worth it for the longer
+// blocks' larger part and from 2^26 elements on (GPT-2 small, 96M elements in rows of 768 and
+// 28M of 3072: 150 us in one launch, 170 in two; 1.5B elements, 268M of them in rows of 8192:
+// 1.17 ms either way).
+enum : int32_t { kHistVec = 1, kHistStream = 2, kHistLong = 4 };
+inline int32_t hist_ways(int64_t regs, int64_t longer, bool other)
+{
+    int32_t ways = (regs ? kHistVec : 0) | (other ? kHistStream : 0);
+    if (longer) ways |= longer <= regs && longer < (int64_t(1) << 26) ? kHistLong : kHistStream;
+    return ways;
 }
 
 struct HistBlock {
@@ -123,8 +142,7 @@ hipError_t launch_step_g_hist(int gdtype, int code_bits, const Tile* tiles, int6
 // launch_hist_h_absmax over each KIND_H class range writes am_partials[first + chunk].
 hipError_t launch_hist_h_absmax(const Tile* tiles, const HTile* htiles, int64_t n_tiles,
                                 const Seg* segs, float* am_partials, hipStream_t stream);
-// `ways` says which of the two kernels have tiles in the range (hist_by_vectors).
-enum : int32_t { kHistVec = 1, kHistStream = 2 };
+// `ways`: hist_ways of the range.
 hipError_t launch_histogram(const Tile* tiles, int64_t n_tiles, const int32_t* tile_kind,
                             const HTile* htiles, const float* am_partials, const Seg* segs,
                             int32_t nbins, uint64_t* hist, int32_t ways, hipStream_t stream);

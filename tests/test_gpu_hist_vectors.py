@@ -6,7 +6,8 @@ import pytest
 
 pytestmark = pytest.mark.gpu
 
-# vectors of a block: lane groups (<= 32), 1, 2, 4 and 8 a lane, longer, and a streamed one
+# vectors of a block: lane groups (<= 32), 1, 2, 4 and 8 a lane, longer (by vectors only where
+# the shorter blocks hold at least as many elements), and a streamed one
 PERIODS = [4, 8, 36, 128, 132, 256, 260, 512, 516, 1024, 1028, 2048, 2052, 6148, 8192, 8196, 30]
 
 
@@ -26,7 +27,8 @@ def _expect(grads, periods, bins):
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("shift", [0, 1])
 @pytest.mark.parametrize("bits", [8, 4])
-def test_histogram_of_uniform_blocks(bf16, shift, bits):
+@pytest.mark.parametrize("rows", [41, 400])   # the longer blocks hold most elements, or the fewer
+def test_histogram_of_uniform_blocks(bf16, shift, bits, rows):
     import torch
 
     import paper_2606_13894_amd as gf
@@ -35,7 +37,7 @@ def test_histogram_of_uniform_blocks(bf16, shift, bits):
     dt = torch.bfloat16 if bf16 else torch.float32
     grads = []
     for i, p in enumerate(PERIODS):
-        n = p * (41 if p < 1000 else 7)
+        n = p * (rows if p < 1000 else 7)
         buf = torch.randn(n + shift, generator=gen, device="cuda").mul_(10.0 ** (i % 5 - 2)).to(dt)
         g = buf[shift:]
         g[p:2 * p] = 0.0            # a zero block counts nothing
