@@ -79,12 +79,17 @@ def test_each_iteration_teacher_forced(batch, m, n):
     print(f"{(batch, m, n)}: largest share of one-step flips {worst:.2e}")
 
 
-def test_big_tile_iterations():
-    """The 256 x 256 tile (one workgroup per CU, 4 x 4 accumulators per wave) and its
-    split Gram: six 1024 x 2048 matrices take the big tile in the Gram product (split 4
-    ways over K) and in the combine. Three iterations, teacher-forced, every batch entry."""
+# Shapes of the 256 x 256 tile (one workgroup per CU, 4 x 4 accumulators per wave), all with it
+# in the combine: beside a Gram product in small tiles, in big tiles split over K (with the
+# reduce at tile 256), and in big tiles unsplit. tests/test_ns_plan_cpu.py holds the plan to
+# that.
+BIG_SHAPES = [(6, 1024, 2048), (3, 1024, 4096), (16, 1024, 1024)]
+
+
+@pytest.mark.parametrize("batch,m,n", BIG_SHAPES, ids=lambda v: str(v))
+def test_big_tile_iterations(batch, m, n):
+    """Three iterations, teacher-forced, every batch entry."""
     dev = _dev()
-    batch, m, n = 6, 1024, 2048
     x = _x0(batch, m, n, seed=11, dev=dev)
     worst = 0.0
     for k in range(3):
@@ -94,7 +99,7 @@ def test_big_tile_iterations():
         for bi in range(batch):
             worst = max(worst, _check_iteration(xi[bi], yo[bi], f"big tile it {k} b {bi}"))
         x = y
-    print(f"big tile: largest share of one-step flips {worst:.2e}")
+    print(f"big tile {(batch, m, n)}: largest share of one-step flips {worst:.2e}")
 
 
 def test_steps_chain_bitwise():

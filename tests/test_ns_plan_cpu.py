@@ -5,6 +5,7 @@ ping-pong parities passes the library's own check, every work item decodes to a 
 in-range tile, and every operand access the kernel's predicates allow stays inside the
 lane buffer behind its pointer (tests/ns_plan_check.cpp)."""
 import os
+import re
 import subprocess
 
 import pytest
@@ -48,7 +49,6 @@ def test_lanes_balance_and_order(checker, name):
     estimated time (each group to the lane with less so far, longest first: the two differ
     by at most their longest group); every lane runs longest first, and every group is on
     one lane."""
-    import re
     w = W.get(name)
     rc, out = _run(checker, [(t.rows, t.numel) for t in w.tensors])
     assert rc == 0, out
@@ -111,6 +111,18 @@ def test_odd_shapes_stay_in_bounds(checker):
     rc, out = _run(checker, [(r, r * c) for r, c in shapes])
     assert rc == 0, out
     assert out.strip().splitlines()[-1].startswith("ok:"), out
+
+
+@pytest.mark.parametrize("batch,m,n,gram,split",
+                         [(6, 1024, 2048, 128, False), (3, 1024, 4096, 256, True),
+                          (16, 1024, 1024, 256, False)])
+def test_big_tile_shapes(checker, batch, m, n, gram, split):
+    """The shapes whose big tiles the GPU tests compare element by element take them: the Gram
+    product's tile, whether it is split over K, and the big tile in the combine."""
+    rc, out = _run(checker, [(m, m * n)] * batch)
+    assert rc == 0, out
+    g = re.search(r"Gram splits (\d+) .*tiles (\d+) / \d+ / (\d+),", out)
+    assert (int(g.group(2)), int(g.group(1)) > 1, int(g.group(3))) == (gram, split, 256), out
 
 
 def test_a_bad_shape_is_refused(checker):
