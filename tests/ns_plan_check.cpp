@@ -179,6 +179,8 @@ int main()
                 NsGemmArgs prods[3];
                 int64_t avail[3][6];
                 ns_iteration_products(sh, lb, z, cur, 3.4445f, -4.775f, 2.0315f, prods, avail);
+                // a dense X in place of the lane's buffer (gefen_newton_schulz) ends with its rows
+                avail[0][0] = avail[0][1] = avail[2][3] = sh.count * sh.m * sh.ldx;
                 const char* names[3] = {"Gram", "poly", "combine"};
                 for (int k = 0; k < 3; ++k) {
                     why = walk(prods[k], avail[k], names[k]);

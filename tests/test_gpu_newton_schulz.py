@@ -102,6 +102,36 @@ def test_big_tile_iterations(batch, m, n):
     print(f"big tile {(batch, m, n)}: largest share of one-step flips {worst:.2e}")
 
 
+@pytest.mark.parametrize("steps", [1, 2, 5])
+@pytest.mark.parametrize("batch,m,n", [(2, 96, 1024), (1, 130, 256), (2, 96, 1000), (3, 17, 33),
+                                       (2, 1, 256), (2, 1, 300)], ids=lambda v: str(v))
+def test_output_in_place_overlapping_and_misaligned(batch, m, n, steps):
+    """Where input and output lie changes no bit: the output over the input, beside it, over a
+    part of it from either side, and either one off its 16-byte alignment (n a multiple of
+    64, where aligned matrices are used in place, and other n). Elsewhere the input and what
+    surrounds the output stay as they were."""
+    dev = _dev()
+    x = _x0(batch, m, n, seed=17 * m + n, dev=dev)
+    size = x.numel()
+    bits = x.view(torch.int16).flatten().clone()
+    want = gf.newton_schulz(x, steps=steps).view(torch.int16).flatten()
+    torch.cuda.synchronize()
+    assert torch.equal(x.view(torch.int16).flatten(), bits)
+    pad = (size + 127) // 64 * 64
+    for x_at, out_at in [(0, 0), (0, size), (size, 0), (0, 8), (8, 0), (0, 64), (64, 0),
+                         (0, size - 8), (0, pad + 1), (pad + 1, 0), (1, pad + 3), (1, 1), (3, 1)]:
+        buf = torch.full((2 * pad + 64,), -2, dtype=torch.int16, device=dev)
+        buf[x_at:x_at + size] = bits
+        expect = buf.clone()
+        expect[out_at:out_at + size] = want
+        flat = buf.view(torch.bfloat16)
+        out = flat[out_at:out_at + size].view(batch, m, n)
+        got = gf.newton_schulz(flat[x_at:x_at + size].view(batch, m, n), steps=steps, out=out)
+        torch.cuda.synchronize()
+        assert got.data_ptr() == out.data_ptr()
+        assert torch.equal(buf, expect), (x_at, out_at)
+
+
 def test_steps_chain_bitwise():
     """Five iterations in one call equal five calls of one iteration, bit for bit, and a
     repeated call gives the same bits (no order-dependent accumulation)."""
