@@ -292,8 +292,9 @@ int gefen_profile_end(gefen_state* st, int32_t cap, int32_t* n_classes, int32_t*
  *          row-major (a 1-D tensor is 1 x numel). rows[i] must divide numel_i.
  * Allocates the bfloat16 momentum matrix (2 bytes per parameter) and the Newton-Schulz
  * buffers of each of three lanes, sized for the lane's largest group of tensors that share
- * one wide shape (X and X^T twice, the two m x m products: about 8 bytes per element of
- * that group), and checks every matrix product of the steps against them on the host;
+ * one wide shape (X and twice X^T, 6 bytes per element of that group, and the two m x m
+ * products, 4 m / n more, both sides rounded up to 64; where the Gram product is split over
+ * K also 4 bytes per element of an m x m matrix and part), and checks every matrix product of the steps against them on the host;
  * synchronises `stream`. Call once per state.
  * Errors: EINVAL (NULL, count mismatch, rows, second call, a matrix side above
  * 2^31 - 4096), ENOMEM, EHIP.
@@ -346,8 +347,10 @@ int gefen_muon_profile_end(gefen_state* st, int32_t* steps, double* codec_ms, do
  *         at x_in + b * m * n, 1 <= m <= n <= 2^31 - 4096, batch in [1, 65535].
  *  x_out  device uint16[batch * m * n], same layout; may equal x_in.
  *  steps  in [0, 100] (0 copies x_in to x_out); a, b, c finite.
- * Asynchronous on `stream`; its workspace (4 to 6 bytes per element of the batch) is
- * allocated and freed stream-ordered on `stream`.
+ * Asynchronous on `stream`; its workspace is allocated and freed stream-ordered on
+ * `stream`: 4 bytes per element of the batch for X^T (6 with X, where n is no multiple of 64 or
+ * a matrix is off 16 bytes or overlaps the other in part), 4 m / n for the two m x m
+ * products, both sides rounded up to 64, and 4 m / n per part of a Gram product split over K.
  * Errors: EINVAL (NULL, sizes, steps, coefficients), ENOMEM, EHIP.
  * ---------------------------------------------------------------------------- */
 int gefen_newton_schulz(const uint16_t* x_in, uint16_t* x_out, int32_t batch, int64_t m,

@@ -660,7 +660,7 @@ __device__ __forceinline__ double wave_min(double v)
 // Where rows may not be pruned (counts times bins of 2^50 or more: histograms accumulated
 // over many steps) every row takes its whole window, 2.1e9 candidates at 4096 bins and 256
 // entries, here and in k_dp_run; dp_cost_below spares most of them the division, and the
-// windows are read once. The whole DP then takes 3.4 ms (17.1 ms with the windows taken chunk
+// windows are read once. The whole DP then takes 3.3 ms (17.1 ms with the windows taken chunk
 // by chunk twice as below, 4.7 ms for the full scan of a launch a level).
 //
 // The candidates fall from 1.9e9 to 5e7 at b = 4096, k = 256, and a level is bound by its

@@ -123,7 +123,7 @@ struct gefen_state {
     // stream, the others on streams of the library's own (forked after the norms, joined
     // at the end of the step). Each lane has its own Newton-Schulz buffers.
     struct MuonLane {
-        NsLaneBuffers buf{};            // X and X^T (ping-pong), A, B, split-K partials
+        NsLaneBuffers buf{};            // X, X^T (ping-pong), A, B, split-K partials
         NsLaneSizes size;
         std::vector<int32_t> groups;    // indices into muon_groups, in launch order
     };
@@ -1196,8 +1196,10 @@ float host_bf16_value(float x)
 
 // One Newton-Schulz iteration of a shape group on a lane's buffers (ns_plan.h):
 // A = X X^T, B = b A + c A A, X' = a X + B X, each a bfloat16 product with float32
-// accumulation; `cur` selects the ping-pong buffers that hold X and X^T.
-// After the last iteration only the orientations that are read need to be written.
+// accumulation; `cur` selects the ping-pong buffer that holds X^T (x[0] and x[1] are one
+// buffer, or the caller's input and output: only the Gram product reads X, before the combine
+// writes the next one). After the last iteration only the orientations that are read need to
+// be written.
 int ns_iteration(const NsLaneBuffers& lb, const NsLaneSizes& z, const NsShape& sh, int cur,
                  float a, float b, float c, hipStream_t stream, bool want_x = true,
                  bool want_xt = true)

@@ -50,21 +50,6 @@ struct CodebookDev {
     int32_t ng;
 };
 
-// Histogram bin (Alg. 3) of gradient g in a block whose largest |g| is a > 0: the bin of
-// x = g / a among nbins equal bins of [-1, 1], the last one closed; half_nb = nbins / 2.
-// Evaluated in float64 (these sources are built with contraction off), so that the
-// histogram kernel and the step kernels that take the histogram on the way bin every
-// element identically. (A float32 estimate with a float64 evaluation near bin edges
-// measured slower in both kernels: a wave almost always holds some lane near an edge.)
-//
-// The quotient is the correctly rounded g / a without a division per element: with inv =
-// RN(1 / a) once per block, q = RN(g inv) is within 2 ulp, r = g - q a is exact (a multiple
-// of ulp(q) times the last place of a, at most 2^25 of them: a has 24 bits), and q + r inv
-// is off by less than 2^-51 ulp before its one rounding. The quotient of two 24-bit numbers
-// lies on no rounding boundary of float64 and no nearer to one than 2^-25 ulp, so that
-// rounding is g / a's. float32 values leave the exponents far from float64's limits. An
-// infinite a takes zeros instead: finite g gives x = 0, infinite g a NaN, as g / a does.
-// (Three multiply-adds against about a dozen dependent operations of the division.)
 // Tiles whose blocks the histogram kernel takes by 4-element vectors from the block's first
 // element on: uniform blocks of whole vectors that one workgroup's tile holds whole, of at
 // most `longest` elements: kHistVecBlock, what its registers hold, or any (hist_ways).
@@ -91,6 +76,21 @@ inline int32_t hist_ways(int64_t regs, int64_t longer, bool other)
     return ways;
 }
 
+// Histogram bin (Alg. 3) of gradient g in a block whose largest |g| is a > 0: the bin of
+// x = g / a among nbins equal bins of [-1, 1], the last one closed; half_nb = nbins / 2.
+// Evaluated in float64 (these sources are built with contraction off), so that the
+// histogram kernel and the step kernels that take the histogram on the way bin every
+// element identically. (A float32 estimate with a float64 evaluation near bin edges
+// measured slower in both kernels: a wave almost always holds some lane near an edge.)
+//
+// The quotient is the correctly rounded g / a without a division per element: with inv =
+// RN(1 / a) once per block, q = RN(g inv) is within 2 ulp, r = g - q a is exact (a multiple
+// of ulp(q) times the last place of a, at most 2^25 of them: a has 24 bits), and q + r inv
+// is off by less than 2^-51 ulp before its one rounding. The quotient of two 24-bit numbers
+// lies on no rounding boundary of float64 and no nearer to one than 2^-25 ulp, so that
+// rounding is g / a's. float32 values leave the exponents far from float64's limits. An
+// infinite a takes zeros instead: finite g gives x = 0, infinite g a NaN, as g / a does.
+// (Three multiply-adds against about a dozen dependent operations of the division.)
 struct HistBlock {
     double a, inv;
 };

@@ -103,7 +103,10 @@ struct NsShape {
 // takes less), start and epilogue, and for a split the float32 partials of the upper tiles,
 // written and read again, and the launch that adds them up. (Rates from the model shapes:
 // a split that only fills the rounds better does not pay for its partials. 6 x 2048 x 8192:
-// 216 big tiles on 256 units in one round 0.25 ms, split 3 ways 0.29 + 0.11 ms.)
+// 216 big tiles on 256 units in one round 0.25 ms, split 7 ways, which fills the rounds best,
+// 0.29 + 0.11 ms. The rate of lone small tiles is that of few tiles with long sums; where
+// they fill most of the units with short ones it is too high by half: 3 x 1500 x 2113, 234
+// tiles of 34 stages, 33 us for an estimate of 50.)
 constexpr double kNsStageBigUs = 1.95, kNsStagePairUs = 1.7, kNsStageLoneUs = 1.2;
 constexpr double kNsTileUs = 9.0, kNsReduceUs = 6.0, kNsPartialBytesPerUs = 6.0e6;
 
@@ -135,11 +138,11 @@ inline int32_t ns_gram_splits(int64_t count, int64_t m, int64_t ldx, int tile)
     return static_cast<int32_t>(best);
 }
 
-// The big tile for a product of M x N outputs (upper tiles only when symmetric) when both
-// sides hold at least four big tiles and its workgroups fill at least 75 % of their
-// rounds; else the small tile. (Measured on the model shapes: at M = 768 the small tile
-// is faster for every product -- the MLP combine 186 against 231 us, the Gram 72 against
-// 154 us with its split -- and at M = 2048 the big one by about 8 %.)
+// The big tile for a polynomial product or a combine of M x N outputs (upper tiles only when
+// symmetric) when both sides hold at least four big tiles and its workgroups fill at least
+// 75 % of their rounds; else the small tile. (Measured on the model shapes, both tiles with
+// an earlier conversion to bfloat16: at M = 768 the small tile is faster -- the MLP combine
+// 186 against 231 us, 168 now -- and at M = 2048 the big one by about 8 %.)
 inline int ns_pick_tile(int64_t count, int64_t M, int64_t N, bool sym)
 {
     if (M < 4 * kNsTileBig || N < 4 * kNsTileBig) return kNsTileSmall;
@@ -155,7 +158,7 @@ inline NsShape ns_shape(int64_t count, int64_t m, int64_t n)
     s.kchunk = static_cast<int32_t>(s.ldx);
     if (m < 2) return s;   // vectors have no matrix products
     // the Gram product: the tile whose estimate with its own best split is lower (3 x 1500 x
-    // 2113: 78 small tiles a matrix unsplit 32 us, 21 big ones split 4 ways 30 + 17 us)
+    // 2113: 78 small tiles a matrix unsplit 33 us, 21 big ones split 4 ways 30 + 17 us)
     s.splits = ns_gram_splits(count, m, s.ldx, kNsTileSmall);
     if (m >= 4 * kNsTileBig) {
         const int32_t sb = ns_gram_splits(count, m, s.ldx, kNsTileBig);
@@ -540,7 +543,7 @@ inline NsLaneSizes ns_lane_sizes(const std::vector<NsGroup>& groups,
 }
 
 // The three products of an iteration on a lane's buffers (x[cur], xt[cur] hold X and
-// X^T), and the elements available behind each of their pointers (P, Q, E, O, Ot,
+// X^T; x[0] and x[1] may be one buffer), and the elements available behind each of their pointers (P, Q, E, O, Ot,
 // partial), for ns_check.
 struct NsLaneBuffers {
     uint16_t* x[2];
